@@ -14,18 +14,17 @@
 // for Hermitian A, B, and det of the pair mean by the row-0 real-part
 // expansion (Eq. detr).  Windows are clipped at the image border.
 //
-// Blocks cover (TW CPL) x TH output pixels.  For window row offset dy the
-// block's lanes need the band of TH input rows y0 + dy .. y0 + dy + TH - 1,
-// each TW CPL + 2r columns wide (covariance and inverse or log2 det,
-// structure of arrays in LDS).  Consecutive bands share TH - 1 rows, so the
-// band is a ring of TH row slots: the first dy stages TH rows, every later dy
-// stages only its new bottom row into the slot of the row no lane needs any
-// more, and each input row is read from memory once per block (TH + 2r rows
-// per TH output rows).  Then every lane sweeps the horizontal neighbours of
-// its CPL adjacent outputs in its row of the band.
+// A wave owns TW columns of G output rows, a lane one column of them.  It
+// walks down the G + 2r input rows its outputs' windows cover: a row's TW + 2r
+// columns (covariance, and what the distance needs beside it) are staged in
+// LDS, and every lane then sweeps its 2r + 1 neighbours there, each neighbour
+// read once for the lane's G outputs.  Where an image has too few tiles to fill
+// the chip, the S waves of a block share one tile: each takes a run of its
+// input rows, and their sums are added in row order at the end.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/polsar.h"
 #include "common.hpp"
@@ -33,7 +32,7 @@
 namespace {
 using polsar_dev::xcd_tile;
 
-constexpr int TW = 64, LH = 4, TH = LH, MAX_R = 16;
+constexpr int TW = 64, MAX_R = 16;
 
 struct NlmArgs {
   const void* z;
@@ -59,162 +58,278 @@ template <class T> __device__ __forceinline__ T log2_(T x);
 template <> __device__ __forceinline__ float log2_(float x) { return log2f(x); }
 template <> __device__ __forceinline__ double log2_(double x) { return log2(x); }
 
-// DIST 0: symmetrized Kullback-Leibler (F = 18 staged values per pixel:
-// Z and Z^-1); DIST 1: Bhattacharyya (F = 10: Z and log2 det Z).  The
-// block's LH x TW lanes own a tile of LH rows and TW * CPL columns: lane
-// (tx, ty) computes the outputs of columns CPL tx + j, j < CPL, of row ty.
-// With CPL = 2 each neighbour column read from LDS serves both of the lane's
-// outputs (2r + 2 reads of 18 values for 2 (2r + 1) pairs); the band then
-// keeps even and odd columns in two halves of its row, so that the lanes'
-// reads, two columns apart, fall on consecutive words.
-template <class T, int DIST, int CPL>
-__global__ __launch_bounds__(TW * LH) void k_nlm(NlmArgs a) {
-  constexpr int F = DIST == 0 ? 18 : 10;
-  // the band, F x TH rows x BW columns; a compile-time row length keeps
-  // every band access at a fixed offset from one address per lane
-  constexpr int BW = TW * CPL + 2 * MAX_R;
-  constexpr int HALF = BW / 2;  // CPL 2: odd columns from here (BW is even)
-  static_assert(CPL == 1 || (CPL == 2 && BW % 2 == 0), "one or two columns per lane");
-  __shared__ T band[F * TH * BW];
-  auto at = [](int col) { return CPL == 2 ? ((col & 1) ? HALF + (col >> 1) : (col >> 1)) : col; };
+// Orders a wave's LDS writes before its lanes' reads and the other way
+// round: a band is shared by the lanes of one wave only.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Adjugate planes and determinant of a packed FP32 matrix, formed in FP64,
+// where its products are exact, and rounded once.
+__device__ __forceinline__ void adjugate_det(const float* z, float* adj, float& det) {
+  double zd[9], c[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) zd[k] = (double)z[k];
+  px::cofactors_plain(zd, c);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) adj[k] = (float)c[k];
+  det = (float)px::det_from_cofactors(zd, c);
+}
+
+// DIST 0: symmetrized Kullback-Leibler, one chain of 18 FMAs over Z and Z^-1
+// of both pixels.  DIST 1: Bhattacharyya; in FP32 the determinant of the pair's
+// sum is taken by multilinearity,
+//   det(P + Q) = det P + det Q + tr(adj(P) Q) + tr(adj(Q) P),
+// with each pixel's adjugate formed once (in FP64, so that only its rounding
+// is left): 20 operations per pair where the sum's own cofactors take 29, and
+// an error against 64 bits of 2.5-4.8e-7 where those had 5-29e-7 (images of
+// 37x70 to 1024x1024, radius 2 to 11).  FP64 keeps the sum's cofactors.
+//
+// Bound by VALU issue: two waves of a SIMD issue FP32 operations in
+// alternation, so a neighbour costs about 2.5 cycles per operation and wave
+// against 30 (KL) operations, an exponential (8 cycles) and its share of the
+// LDS reads, 20 words in five 128-bit reads over the lane's G outputs.  G
+// outputs per lane divide the LDS reads and the rows staged per output by G;
+// single-wave tiles need no barrier.  KL in FP32, 2048x2048, r = 11: 1.61 ms
+// at G = 3 (127 registers, four waves per SIMD), 1.74 at G = 2, 2.12 at G = 1,
+// 1.96 at G = 4 (two waves), against 2.18 ms for four-wave blocks over a ring
+// of rows with two columns per lane.  FP32 matrix instructions (4x4x1) for
+// both contractions gave the same bits at 2.40 ms: they share the vector
+// units' rate.
+template <class T, int DIST, int G, int S>
+__global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
+  constexpr bool MIX = DIST == 1 && std::is_same<T, float>::value;
+  // staged values per pixel: Z, then Z^-1 (KL), or adj Z, det Z and its
+  // logarithm (MIX), or the logarithm; and the features an output keeps
+  constexpr int F = DIST == 0 ? 18 : MIX ? 20 : 10, NP = DIST == 0 || MIX ? 18 : 9;
+  constexpr int E = 16 / sizeof(T), FQ = (F + E - 1) / E;  // values per 16-byte LDS access
+  typedef T VT __attribute__((ext_vector_type(E)));
+  // a compile-time row length keeps every access at a fixed offset from one
+  // address per lane; afterwards a band holds its wave's sums
+  constexpr int BW = TW + 2 * MAX_R;
+  constexpr int BAND = FQ * BW * E > 10 * G * TW ? FQ * BW * E : 10 * G * TW;
+  __shared__ __align__(16) T bands[S][BAND];
   const T* __restrict__ Z = (const T*)a.z;
   const T* __restrict__ A = (const T*)a.aux;
-  const int tx = threadIdx.x % TW, ty = threadIdx.x / TW;
-  const unsigned t = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  const int64_t x0 = (int64_t)(t % gridDim.x) * (TW * CPL), y0 = (int64_t)(t / gridDim.x) * TH;
-  const int64_t py = y0 + ty;
-  const int r = a.r, bw = TW * CPL + 2 * r;
+  const int lane = threadIdx.x % TW, part = threadIdx.x / TW;
+  VT* band = (VT*)bands[part];
+  const unsigned tile = xcd_tile((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
+                                 gridDim.x * gridDim.y * gridDim.z);
+  const int64_t x0 = (int64_t)(tile % gridDim.x) * TW, y0 = (int64_t)(tile / gridDim.x) * G;
+  if (y0 >= a.H) return;  // the grid's rows past the last tile row
+  const int64_t px = x0 + lane;
+  const int r = a.r, nc = TW + 2 * r;
   const T N = (T)a.n_looks;
   const T log2e = (T)1.4426950408889634;
-  // this lane's pixels: Z_p with the off-diagonal doubled (for tr(Q^-1 P)),
-  // and Z_p^-1 with the off-diagonal doubled, or log2 det Z_p; each one's
-  // window of staged columns [d0, d1] (clipped at the image's sides)
-  bool valid[CPL];
-  int d0[CPL], d1[CPL];
-  T zp2[CPL][9], ip2[CPL][9], lp[CPL], acc[CPL][9], wsum[CPL];
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    const int64_t px = x0 + CPL * tx + j;
-    valid[j] = px < a.W && py < a.H;
-    lp[j] = T(0);
-    wsum[j] = T(0);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) { zp2[j][k] = T(0); ip2[j][k] = T(0); acc[j][k] = T(0); }
-    // staged column of neighbour dx: CPL tx + j + dx + r
-    const int lo = px >= r ? -r : (int)-px;
-    const int hi = a.W - 1 - px >= r ? r : (int)(a.W - 1 - px);
-    d0[j] = j + lo + r;
-    d1[j] = j + hi + r;
-    if (valid[j]) {
-      const int64_t i = py * a.W + px;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) zp2[j][k] = Z[k * a.zp + i] * (k < 3 ? T(1) : T(2));
-      if (DIST == 0) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) ip2[j][k] = A[k * a.ap + i] * (k < 3 ? T(1) : T(2));
-      } else {
-        lp[j] = log2_(A[i]);
-      }
-    }
-  }
-  // the columns this lane reads: the union of its outputs' windows
-  int dlo = 1 << 30, dhi = -1;
-#pragma unroll
-  for (int j = 0; j < CPL; ++j)
-    if (valid[j]) {
-      dlo = d0[j] < dlo ? d0[j] : dlo;
-      dhi = d1[j] > dhi ? d1[j] : dhi;
-    }
-  // w = exp2(alpha * s + beta): KL s = t1 + t2; B s = log2 det(Zp + Zq) - (lp + lq)/2
+  // w = exp2(alpha * s + beta): KL s = the two traces; B s = log2 det(Zp + Zq) - (lp + lq)/2
   const T alpha = DIST == 0 ? -N * log2e / (T(2) * (T)a.h) : -N / (T)a.h;
   const T beta = DIST == 0 ? T(3) * N * log2e / (T)a.h : T(3) * N / (T)a.h;
-  // input row i of the block (global row y0 - r + i) lives in ring slot i % TH
-  auto stage = [&](int i, int col) {
-    const int64_t gy = y0 - r + i, gx = x0 - r + col;
-    const int slot = i % TH;
-    if (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) {
-      const int64_t g = gy * a.W + gx;
-      const int c = at(col);
+
+  // the outputs' features: Z_p with the off-diagonal doubled (for tr(Q^-1 P)
+  // and tr(adj(Q) P)), then Z_p^-1 or adj Z_p likewise; FP64 B: Z_p itself.
+  // lp: log2 det Z_p, in MIX its part of the exponent
+  T P[G][NP], detp[G], lp[G], acc[G][9], ws[G];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) band[(k * TH + slot) * BW + c] = Z[k * a.zp + g];
-      if (DIST == 0) {
+  for (int g = 0; g < G; ++g) {
+    ws[g] = detp[g] = lp[g] = T(0);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) band[((9 + k) * TH + slot) * BW + c] = A[k * a.ap + g];
-      } else {
-        band[(9 * TH + slot) * BW + c] = log2_(A[g]);
+    for (int k = 0; k < 9; ++k) acc[g][k] = T(0);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) P[g][k] = T(0);
+    if (px < a.W && y0 + g < a.H) {
+      const int64_t i = (y0 + g) * a.W + px;
+      T z[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        z[k] = Z[k * a.zp + i];
+        P[g][k] = NP == 18 ? z[k] * (k < 3 ? T(1) : T(2)) : z[k];
       }
-    }
-  };
-  for (int dy = -r; dy <= r; ++dy) {
-    __syncthreads();  // every lane is done with the slot about to be refilled
-    if (dy == -r) {
-      for (int idx = threadIdx.x; idx < TH * bw; idx += TW * LH) stage(idx / bw, idx % bw);  // the first band
-    } else {
-      for (int col = threadIdx.x; col < bw; col += TW * LH) stage(TH - 1 + dy + r, col);  // its new bottom row
-    }
-    __syncthreads();
-    // rows y + dy outside the image are not read (an unstaged slot holds
-    // stale values)
-    const int64_t qy = py + dy;
-    if (qy < 0 || qy >= a.H || dhi < 0) continue;
-    const int sl = (ty + dy + r) % TH;  // this lane's input row y0 + ty + dy
-    for (int d = dlo; d <= dhi; ++d) {
-      const int c = at(CPL * tx + d);
-      T q[9];
+      if constexpr (DIST == 0) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) q[k] = band[(k * TH + sl) * BW + c];
-      T qi[DIST == 0 ? 9 : 1];
-      if (DIST == 0) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) qi[k] = band[((9 + k) * TH + sl) * BW + c];
+        for (int k = 0; k < 9; ++k) P[g][9 + k] = A[k * a.ap + i] * (k < 3 ? T(1) : T(2));
       } else {
-        qi[0] = band[(9 * TH + sl) * BW + c];
-      }
+        lp[g] = log2_(A[i]);
+        if constexpr (MIX) {
+          lp[g] = fma(T(-0.5) * alpha, lp[g], beta);
+          T adj[9];
+          adjugate_det(z, adj, detp[g]);
 #pragma unroll
-      for (int j = 0; j < CPL; ++j) {
-        if (!valid[j] || d < d0[j] || d > d1[j]) continue;
-        T s;
-        if (DIST == 0) {
-          // tr(Zp^-1 Zq) + tr(Zq^-1 Zp) as one chain of 18 FMAs
-          T tt = ip2[j][0] * q[0];
-          tt = fma(qi[0], zp2[j][0], tt);
-#pragma unroll
-          for (int k = 1; k < 9; ++k) {
-            tt = fma(ip2[j][k], q[k], tt);
-            tt = fma(qi[k], zp2[j][k], tt);
-          }
-          s = tt;
-        } else {
-          // det(Z_p + Z_q): the off-diagonal of zp2 is doubled, halve it back
-          T mm[9];
-#pragma unroll
-          for (int k = 0; k < 9; ++k) mm[k] = zp2[j][k] * (k < 3 ? T(1) : T(0.5)) + q[k];
-          T cf[9];
-          px::cofactors_plain(mm, cf);
-          s = log2_(px::det_from_cofactors(mm, cf)) - T(0.5) * (lp[j] + qi[0]);
+          for (int k = 0; k < 9; ++k) P[g][9 + k] = adj[k] * (k < 3 ? T(1) : T(2));
         }
-        const T w = exp2_(alpha * s + beta);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) acc[j][k] += w * q[k];
-        wsum[j] += w;
       }
     }
   }
+  // this lane's window of staged columns, clipped at the image's sides; none
+  // past the last column
+  int dlo = px < r ? r - (int)px : 0;
+  const int64_t right = a.W - 1 - px;
+  int dhi = right < r ? (int)right + r : 2 * r;
+  if (px >= a.W) { dlo = 1; dhi = 0; }
+  const bool inner = x0 >= r && x0 + TW - 1 + r < a.W;  // no lane's window is clipped
+
+  auto read = [&](int col, T (&q)[F]) {
 #pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    if (!valid[j]) continue;
-    const int64_t i = py * a.W + x0 + CPL * tx + j;
-    const T inv = T(1) / wsum[j];
+    for (int k = 0; k < FQ; ++k) {
+      const VT v = band[k * BW + col];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) ((T*)a.out)[k * a.op + i] = acc[j][k] * inv;
-    if (a.wsum) ((T*)a.wsum)[i] = wsum[j];
+      for (int e = 0; e < E; ++e)
+        if (k * E + e < F) q[k * E + e < F ? k * E + e : 0] = v[e];
+    }
+  };
+  auto pair = [&](int g, const T (&q)[F]) {
+    T w;
+    if constexpr (DIST == 0) {
+      T tt = P[g][9] * q[0];
+      tt = fma(q[9], P[g][0], tt);
+#pragma unroll
+      for (int k = 1; k < 9; ++k) {
+        tt = fma(P[g][9 + k], q[k], tt);
+        tt = fma(q[9 + k], P[g][k], tt);
+      }
+      w = exp2_(alpha * tt + beta);
+    } else if constexpr (MIX) {
+      T tt = detp[g] + q[18];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        tt = fma(P[g][9 + k], q[k], tt);
+        tt = fma(q[9 + k], P[g][k], tt);
+      }
+      w = exp2_(fma(alpha, log2_(tt), lp[g] + q[19]));
+    } else {
+      T mm[9], cf[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) mm[k] = P[g][k] + q[k];
+      px::cofactors_plain(mm, cf);
+      w = exp2_(alpha * (log2_(px::det_from_cofactors(mm, cf)) - T(0.5) * (lp[g] + q[9])) + beta);
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[g][k] += w * q[k];
+    ws[g] += w;
+  };
+
+  // input row s of the tile is image row y0 - r + s; row g of the outputs has
+  // it in its window while 0 <= s - g <= 2r
+  const int rows = 2 * r + G;
+  for (int s = part * rows / S; s < (part + 1) * rows / S; ++s) {
+    const int64_t gy = y0 - r + s;
+    if (gy < 0 || gy >= a.H) continue;
+    wave_sync();  // the last row has been read
+    for (int col = lane; col < nc; col += TW) {
+      const int64_t gx = x0 - r + col;
+      if (gx < 0 || gx >= a.W) continue;  // no lane reads this column
+      const int64_t i = gy * a.W + gx;
+      T v[FQ * E];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) v[k] = Z[k * a.zp + i];
+      if constexpr (DIST == 0) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) v[9 + k] = A[k * a.ap + i];
+      } else {
+        v[F - 1] = log2_(A[i]);
+        if constexpr (MIX) {
+          adjugate_det(v, v + 9, v[18]);
+          v[F - 1] *= T(-0.5) * alpha;
+        }
+      }
+#pragma unroll
+      for (int k = F; k < FQ * E; ++k) v[k] = T(0);
+#pragma unroll
+      for (int k = 0; k < FQ; ++k) {
+        VT x;
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = v[k * E + e];
+        band[k * BW + col] = x;
+      }
+    }
+    wave_sync();
+    const int g_lo = s > 2 * r ? s - 2 * r : 0;
+    int g_hi = s < G - 1 ? s : G - 1;
+    if (y0 + g_hi >= a.H) g_hi = (int)(a.H - 1 - y0);
+    if (inner && g_lo == 0 && g_hi == G - 1) {
+#pragma unroll 1
+      for (int d = 0; d <= 2 * r; ++d) {
+        T q[F];
+        read(lane + d, q);
+#pragma unroll
+        for (int g = 0; g < G; ++g) pair(g, q);
+      }
+    } else {
+#pragma unroll 1
+      for (int d = dlo; d <= dhi; ++d) {
+        T q[F];
+        read(lane + d, q);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          if (g >= g_lo && g <= g_hi) pair(g, q);
+      }
+    }
+  }
+
+  auto store = [&](int g, const T (&sum)[9], T total) {
+    const int64_t i = (y0 + g) * a.W + px;
+    const T inv = T(1) / total;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) ((T*)a.out)[k * a.op + i] = sum[k] * inv;
+    if (a.wsum) ((T*)a.wsum)[i] = total;
+  };
+  if constexpr (S == 1) {
+    if (px >= a.W) return;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (y0 + g < a.H) store(g, acc[g], ws[g]);
+  } else {
+    // wave g of the block adds output row g's sums over the parts
+    static_assert(S >= G, "a wave per output row");
+    T* mine = bands[part];
+    wave_sync();
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) mine[(g * 10 + k) * TW + lane] = acc[g][k];
+      mine[(g * 10 + 9) * TW + lane] = ws[g];
+    }
+    __syncthreads();
+    const int g = part;
+    if (g >= G || y0 + g >= a.H || px >= a.W) return;
+    T sum[9], total = bands[0][(g * 10 + 9) * TW + lane];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) sum[k] = bands[0][(g * 10 + k) * TW + lane];
+#pragma unroll
+    for (int p = 1; p < S; ++p) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) sum[k] += bands[p][(g * 10 + k) * TW + lane];
+      total += bands[p][(g * 10 + 9) * TW + lane];
+    }
+    store(g, sum, total);
   }
 }
 
-// Columns per lane: two in FP32 (on the 4096^2 image at r = 11, KL 10.2 ->
-// 9.0 ms, its pairs having been bound by their 18 LDS reads, Bhattacharyya
-// 9.7 -> 9.2 ms); one in FP64, whose KL band would take 92 KB of LDS.
-template <class T, int DIST> constexpr int nlm_cpl() { return sizeof(T) == 4 ? 2 : 1; }
+template <class T, int DIST, int G, int S>
+void go_nlm(const NlmArgs& a, hipStream_t s) {
+  // tile rows beyond a grid's 65535 go to its third dimension
+  const unsigned ny = (unsigned)((a.H + G - 1) / G), nz = (ny + 65534) / 65535;
+  const dim3 grid((unsigned)((a.W + TW - 1) / TW), (ny + nz - 1) / nz, nz);
+  hipLaunchKernelGGL((k_nlm<T, DIST, G, S>), grid, dim3(TW * S), 0, s, a);
+}
+
+// Output rows per lane and waves per tile, by the number of two-row tiles
+// (1024 SIMDs to fill).  KL in FP32 as (rows, waves): 256x256, r = 11 (512
+// tiles): 39 us (2, 8), 49 (2, 4), 151 (2, 1); 450x600, r = 5 (2250 tiles):
+// 46 us (2, 4), 54 (2, 8), 62 (2, 1); 1024x1024, r = 11 (8192): 445 us (2, 4),
+// 436 (3, 4), 490 (3, 1); 1200x1200, r = 5 (11400): 181 us (3, 1), 183 (2, 4);
+// 2048x2048, r = 11: 1607 us (3, 1), 1705 (2, 4).  Three rows only there: B
+// in FP32 ran 2.06 ms with two and 2.09 with three, FP64 has no registers for
+// three.
+template <class T, int DIST>
+void launch_nlm(const NlmArgs& a, hipStream_t s) {
+  const int64_t tiles = ((a.W + TW - 1) / TW) * ((a.H + 1) / 2);
+  constexpr int ROWS = DIST == 0 && std::is_same<T, float>::value ? 3 : 2;
+  if (tiles < 1024) go_nlm<T, DIST, 2, 8>(a, s);
+  else if (tiles < 9216) go_nlm<T, DIST, 2, 4>(a, s);
+  else go_nlm<T, DIST, ROWS, 1>(a, s);
+}
 
 }  // namespace
 
@@ -225,10 +340,8 @@ extern "C" int polsar_nlm_wishart(int dtype, int distance, int64_t height, int64
   if (distance != POLSAR_DIST_KL && distance != POLSAR_DIST_BHATTACHARYYA) return POLSAR_E_ARG;
   if (height < 0 || width < 0 || radius < 0 || radius > MAX_R || !(n_looks > 0.0) || !(h > 0.0))
     return POLSAR_E_ARG;
-  // one block row of the grid per tile row (LH output rows), at most 65535
-  // of them
   const bool kl = distance == POLSAR_DIST_KL;
-  if (width > (1 << 20) || height > (int64_t)LH * 65535) return POLSAR_E_ARG;
+  if (width > (1 << 20) || height > (int64_t)4 * 65535) return POLSAR_E_ARG;
   const int64_t n = height * width;
   const size_t es = dtype == POLSAR_F64 ? 8 : 4;
   const int aux_planes = distance == POLSAR_DIST_KL ? 9 : 1;
@@ -252,16 +365,13 @@ extern "C" int polsar_nlm_wishart(int dtype, int distance, int64_t height, int64
       return POLSAR_E_ALIAS;
   }
   NlmArgs a{z, z_pitch, aux, aux_pitch, out, out_pitch, wsum, height, width, radius, n_looks, h};
-  const int tw = TW * (dtype == POLSAR_F32 ? (kl ? nlm_cpl<float, 0>() : nlm_cpl<float, 1>())
-                                           : (kl ? nlm_cpl<double, 0>() : nlm_cpl<double, 1>()));
-  const dim3 grid((unsigned)((width + tw - 1) / tw), (unsigned)((height + LH - 1) / LH));
   hipStream_t s = (hipStream_t)stream;
   if (dtype == POLSAR_F32) {
-    if (kl) hipLaunchKernelGGL((k_nlm<float, 0, nlm_cpl<float, 0>()>), grid, dim3(TW * LH), 0, s, a);
-    else hipLaunchKernelGGL((k_nlm<float, 1, nlm_cpl<float, 1>()>), grid, dim3(TW * LH), 0, s, a);
+    if (kl) launch_nlm<float, 0>(a, s);
+    else launch_nlm<float, 1>(a, s);
   } else {
-    if (kl) hipLaunchKernelGGL((k_nlm<double, 0, nlm_cpl<double, 0>()>), grid, dim3(TW * LH), 0, s, a);
-    else hipLaunchKernelGGL((k_nlm<double, 1, nlm_cpl<double, 1>()>), grid, dim3(TW * LH), 0, s, a);
+    if (kl) launch_nlm<double, 0>(a, s);
+    else launch_nlm<double, 1>(a, s);
   }
   return hipGetLastError() == hipSuccess ? POLSAR_OK : POLSAR_E_HIP;
 }
