@@ -102,7 +102,7 @@ __device__ __forceinline__ double batch_tile(const BatchArgs& a, const ImgDesc& 
         };
         float o1[1][9][V], d1[1][V];
         int s1[1][V];
-        comp_f32_wave<1, V>(load, valid, o1, d1, s1, q, qs);
+        comp_f32_wave<1, V>(load, valid, o1, d1, s1, q, qs, status || a.counters);
 #pragma unroll
         for (int l = 0; l < V; ++l) {
 #pragma unroll
@@ -117,7 +117,7 @@ __device__ __forceinline__ double batch_tile(const BatchArgs& a, const ImgDesc& 
           T zz[9], xx[9];
 #pragma unroll
           for (int k = 0; k < 9; ++k) zz[k] = z[k][l];
-          st[l] = run_pixel<T, OP>(zz, xx, dt[l]);
+          st[l] = run_pixel<T, OP>(zz, xx, dt[l], status || a.counters);
 #pragma unroll
           for (int k = 0; k < 9; ++k) out[k][l] = xx[k];
           tally(st[l], c0, c1, c2);
@@ -161,7 +161,7 @@ __device__ __forceinline__ double batch_tile(const BatchArgs& a, const ImgDesc& 
       for (int k = 0; k < 9; ++k) zz[k] = Z[k * d.zp + i];
       if (a.do_inv) {
         T xx[9], dt;
-        const int st = run_pixel<T, OP>(zz, xx, dt);
+        const int st = run_pixel<T, OP>(zz, xx, dt, status || a.counters);
         tally(st, c0, c1, c2);
         if (inv)
 #pragma unroll

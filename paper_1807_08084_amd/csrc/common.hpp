@@ -119,9 +119,11 @@ __device__ __forceinline__ void tally(int st, unsigned& c0, unsigned& c1, unsign
 // ------------------------------------------------------------------ ops
 enum Op { ADJ_PLAIN = 0, ADJ_COMP = 1, ADJ_WIDE = 2, CHOL_PLAIN = 3, CHOL_COMP = 4, CHOL_WIDE = 5 };
 
+// want_st: the status is used (where it costs more than the result)
 template <class T, int OP>
-__device__ __forceinline__ int run_pixel(const T (&z)[9], T (&x)[9], T& det) {
+__device__ __forceinline__ int run_pixel(const T (&z)[9], T (&x)[9], T& det, bool want_st) {
   if constexpr (OP == ADJ_PLAIN) return px::adjugate_plain(z, x, det);
+  else if constexpr (OP == ADJ_COMP && sizeof(T) == 4) return px::adjugate_comp(z, x, det, want_st);
   else if constexpr (OP == ADJ_COMP) return px::adjugate_comp(z, x, det);
   else if constexpr (OP == ADJ_WIDE) return px::adjugate_wide(z, x, det);
   else if constexpr (OP == CHOL_PLAIN) return px::cholesky_plain(z, x, det);
@@ -129,15 +131,27 @@ __device__ __forceinline__ int run_pixel(const T (&z)[9], T (&x)[9], T& det) {
   else return px::cholesky_wide(z, x, det);
 }
 
-// ------------------------------------------------------------------ FP32 compensated, shared FP64 queue
-// Compensated FP32 for one lane's U*V pixels (U vectors of V) with the FP64
-// recomputes gathered across the wave: every pixel first takes the FP32
-// step, and a pixel the step rejects is queued in the wave's LDS region
-// (its 9 inputs) right after its step, so its inputs need not stay in
+// Orders the LDS accesses of one wave's lanes: what was written before is
+// read after, and what is read before is overwritten after.  Unlike
+// __syncthreads it waits for no global access: in a one-wave block that
+// barrier still holds the wave until its outstanding stores are done.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ------------------------------------------------------------------ FP32 compensated, shared queue
+// Compensated FP32 for one lane's U*V pixels (U vectors of V) with what the
+// quick form leaves over gathered across the wave: every pixel first takes
+// the quick form, and a pixel whose value it does not carry, or whose status
+// it does not settle where statuses are wanted, is queued in the wave's LDS
+// region (its 9 inputs) right away, so its inputs need not stay in
 // registers.  Then the wave's lanes take one queued pixel each through the
-// FP64 step, and the results go back through LDS to the owning lanes,
-// which store whole vectors.  A wave with nothing rejected skips the
-// queue.  With a fraction p of pixels rejected the FP64 step runs
+// FP32 evaluation (its status) and the error-free one (its value), and the
+// results go back through LDS to the owning lanes,
+// which store whole vectors.  A wave with nothing queued skips the
+// queue.  With a fraction p of pixels queued the rest runs
 // ceil(U V p) times per wave instead of up to U V times; queueing all U
 // vectors of a tile together fills the last round better than queueing
 // each vector on its own.  (Letting the recomputing lanes store their
@@ -148,7 +162,9 @@ __device__ __forceinline__ int run_pixel(const T (&z)[9], T (&x)[9], T& det) {
 // det), stored word-major (word k of entry e at q[k*64*U*V + e], so that
 // each word of a pixel is one LDS access at an immediate offset from the
 // same address and consecutive entries fall in consecutive banks), then
-// 64*U*V status bytes.  valid[u] is false for vectors past the
+// 64*U*V status bytes.  Pixels queued for their value fill it from the front,
+// pixels queued for their status alone from the back, so that each evaluation
+// runs over a dense range.  valid[u] is false for vectors past the
 // end of the image; those take no step and are not queued.  load(u, in)
 // fills the 9 planes of vector u.  Every lane of the wave that is active at
 // the call takes part (ballots); inactive lanes neither queue nor drain.
@@ -156,12 +172,13 @@ constexpr int QUEUE_WORDS = 10;
 
 template <int U, int V, class Load>
 __device__ __forceinline__ void comp_f32_wave(const Load& load, const bool (&valid)[U], float (&out)[U][9][V],
-                                              float (&dt)[U][V], int (&st)[U][V], float* q, uint8_t* qs) {
+                                              float (&dt)[U][V], int (&st)[U][V], float* q, uint8_t* qs,
+                                              bool want_st) {
   constexpr int E = 64 * U * V;  // entries: the stride between a pixel's words
   const int lane = threadIdx.x & 63;
   const unsigned long long below = lane == 0 ? 0ull : ((1ull << lane) - 1ull);
-  unsigned long long mask[U][V];
-  int total = 0;  // the wave's queued pixels
+  unsigned long long mask[U][V], smask[U][V];
+  int total = 0, stotal = 0;  // the wave's pixels queued for their value, and for their status alone
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     // vector u is fetched here (load(u, in)), after the steps of vector
@@ -171,33 +188,45 @@ __device__ __forceinline__ void comp_f32_wave(const Load& load, const bool (&val
     if (valid[u]) load(u, in);
 #pragma unroll
     for (int l = 0; l < V; ++l) {
-      bool need = false;
+      int quick = px::QUICK_ALL;
       st[u][l] = px::ST_OK;
       if (valid[u]) {
         float zz[9], xx[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) zz[k] = in[k][l];
-        need = !px::adjugate_comp_try(zz, xx, dt[u][l]);
+        quick = px::adjugate_comp_quick(zz, xx, dt[u][l]);
 #pragma unroll
         for (int k = 0; k < 9; ++k) out[u][k][l] = xx[k];
       }
+      const bool need = quick == px::QUICK_NONE, sneed = want_st && quick == px::QUICK_VALUE;
       mask[u][l] = __ballot(need);
-      if (need) {
-        const int pos = total + __popcll(mask[u][l] & below);
+      smask[u][l] = __ballot(sneed);
+      if (need || sneed) {
+        const int pos = need ? total + __popcll(mask[u][l] & below) : E - 1 - stotal - __popcll(smask[u][l] & below);
 #pragma unroll
         for (int k = 0; k < 9; ++k) q[k * E + pos] = in[k][l];
       }
       total += __popcll(mask[u][l]);
+      stotal += __popcll(smask[u][l]);
     }
   }
-  if (total == 0) return;  // uniform across the active lanes
+  if (total + stotal == 0) return;  // uniform across the active lanes
   // the active lanes share the queue: rank among them, stride = their count
   const unsigned long long active = __ballot(1);
   const int rank = __popcll(active & below), nact = __popcll(active);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (int e = rank; e < total; e += nact) {
+  wave_sync();
+  if (want_st) {
+#pragma unroll 1
+    for (int i = rank; i < total + stotal; i += nact) {
+      const int e = i < total ? i : E - 1 - (i - total);
+      float zz[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) zz[k] = q[k * E + e];
+      qs[e] = px::adjugate_comp_try(zz) ? px::ST_OK : px::ST_REROUTED;
+    }
+  }
+#pragma unroll 1
+  for (int e = rank; e < total; e += nact) {  // the lane that wrote qs[e]
     float zz[9], xx[9], d;
 #pragma unroll
     for (int k = 0; k < 9; ++k) zz[k] = q[k * E + e];
@@ -205,12 +234,10 @@ __device__ __forceinline__ void comp_f32_wave(const Load& load, const bool (&val
 #pragma unroll
     for (int k = 0; k < 9; ++k) q[k * E + e] = xx[k];
     q[9 * E + e] = d;
-    qs[e] = (uint8_t)sst;
+    if (want_st && qs[e] != px::ST_OK) qs[e] = (uint8_t)sst;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  int base = 0;
+  wave_sync();
+  int base = 0, sbase = E - 1;
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -220,9 +247,11 @@ __device__ __forceinline__ void comp_f32_wave(const Load& load, const bool (&val
 #pragma unroll
         for (int k = 0; k < 9; ++k) out[u][k][l] = q[k * E + pos];
         dt[u][l] = q[9 * E + pos];
-        st[u][l] = qs[pos];
+        if (want_st) st[u][l] = qs[pos];
       }
+      if ((smask[u][l] >> lane) & 1ull) st[u][l] = qs[sbase - __popcll(smask[u][l] & below)];
       base += __popcll(mask[u][l]);
+      sbase -= __popcll(smask[u][l]);
     }
 }
 

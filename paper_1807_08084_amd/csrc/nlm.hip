@@ -30,6 +30,7 @@
 #include "common.hpp"
 
 namespace {
+using polsar_dev::wave_sync;
 using polsar_dev::xcd_tile;
 
 constexpr int TW = 64, MAX_R = 16;
@@ -57,14 +58,6 @@ template <class T> __device__ __forceinline__ T log2_(T x);
 // entries can be subnormal, which log2f scales first)
 template <> __device__ __forceinline__ float log2_(float x) { return log2f(x); }
 template <> __device__ __forceinline__ double log2_(double x) { return log2(x); }
-
-// Orders a wave's LDS writes before its lanes' reads and the other way
-// round: a band is shared by the lanes of one wave only.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Adjugate planes and determinant of a packed FP32 matrix, formed in FP64,
 // where its products are exact, and rounded once.

@@ -286,31 +286,165 @@ PX_HD int adjugate_comp(const double z[9], double x[9], double& det) {
   return classify(det, t, z[0], c[2].hi + c[2].lo);
 }
 
-// Relative threshold on the determinant bound above which an FP32 pixel is
-// recomputed in FP64.
+// Relative threshold on the determinant bound above which an FP32 pixel's
+// status is ST_REROUTED.
 constexpr float REROUTE_REL = 1e-6f;
 
-// Compensated FP32 with selective FP64 recompute.  A pixel whose bound
-// exceeds REROUTE_REL * |det|, or whose det is not positive or not finite,
-// is recomputed by the compensated FP64 path from its exactly widened
-// inputs and rounded to FP32 (status ST_REROUTED when that succeeds).
+// Compensated FP32.  Results come from FP64 arithmetic on the exactly widened
+// inputs, where every cofactor product is exact, in one of two forms:
+// * adjugate_comp_quick: plain sums, for pixels whose determinant is not
+//   small against a d f, so that FP64 rounding stays below FP32's; all but a
+//   few pixels of a well-conditioned image.
+// * adjugate_comp_reroute: error-free sums, for all others.
+// The status says whether FP32 arithmetic alone would have carried the pixel:
+// ST_OK where the compensated FP32 evaluation (adjugate_comp_try) bounds its
+// determinant's error by REROUTE_REL |det|, ST_REROUTED where it does not and
+// FP64 does.  It needs that evaluation only where it is asked for and the
+// pixel is not so well conditioned that ST_OK is certain.
 //
-// adjugate_comp_try: the FP32 step; returns true and the result when the
-// pixel is accepted, false when it must be recomputed (x then holds the
-// scaled FP32 cofactors, which the recompute replaces: scaling every pixel
-// costs less than branching around the scale).
-PX_HD bool adjugate_comp_try(const float z[9], float x[9], float& det, float* bound_out = nullptr) {
-  DW<float> c[9];
-  float rerr[9], bound;
+// Hides that z is what it was, so that what was computed from it before is not
+// kept for what is computed from it again.
+PX_HD void forget_all(float (&z)[9]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile(""
+               : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]), "+v"(z[4]), "+v"(z[5]), "+v"(z[6]), "+v"(z[7]),
+                 "+v"(z[8]));
+#else
+  (void)z;
+#endif
+}
+
+// One term of det_comp with its cofactor, det_comp's steps in its order: x c
+// added to (p, s), the low word returned for later, R, C and X its error sums.
+template <int K>
+PX_HD float try_term(float (&z)[9], float x, float& p, float& s, float& R, float& C, float& X) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  forget_all(z);
+  const float d = z[1], f = z[2], br = z[3], bi = z[4], cr = z[5], ci = z[6], er = z[7], ei = z[8];
+  float rerr;
+  const DW<float> c = K == 3   ? dot3(cr, er, ci, ei, -br, f, rerr)
+                      : K == 4 ? dot3(ci, er, -cr, ei, -bi, f, rerr)
+                      : K == 5 ? dot3(br, er, -bi, ei, -cr, d, rerr)
+                               : dot3(br, ei, bi, er, -ci, d, rerr);
+  const float h = x * c.hi;
+  const float r = fma_(x, c.hi, -h);
+  float q;
+  C = fma_(abs_(x), rerr, C);
+  X = X + abs_(x);
+  two_sum(p, h, p, q);
+  const float t = q + r;
+  s = s + t;
+  R = R + (abs_(t) + abs_(s));
+  return c.lo;
+}
+
+// adjugate_comp_try: whether the compensated FP32 evaluation (cofactors_comp,
+// det_comp) is accurate enough, its determinant's bound within REROUTE_REL
+// |det|, and the pixel positive definite in it.  The cofactors are formed one
+// at a time, which takes a third of the registers.
+PX_HD bool adjugate_comp_try(const float z0[9], float* bound_out = nullptr) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  float z[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) z[k] = z0[k];
   bool ordered = true;
-  cofactors_comp(z, c, rerr, &ordered);
-  det = det_comp(z, c, rerr, bound);
+  float rerr, unused;
+  const DW<float> c0 = dot3<float, true>(z[1], z[2], -z[7], z[7], -z[8], z[8], rerr, &ordered);
+  float p = z[0] * c0.hi;
+  float s = fma_(z[0], c0.hi, -p);
+  float R = 0.0f;
+  float C = abs_(z[0]) * rerr;
+  float X = abs_(z[0]);
+  const float l0 = c0.lo;
+  const float l1 = try_term<3>(z, z[3], p, s, R, C, X);
+  const float l2 = try_term<4>(z, z[4], p, s, R, C, X);
+  const float l3 = try_term<5>(z, z[5], p, s, R, C, X);
+  const float l4 = try_term<6>(z, z[6], p, s, R, C, X);
+  s = fma_(z[0], l0, s);
+  R = R + abs_(s);
+  s = fma_(z[3], l1, s);
+  R = R + abs_(s);
+  s = fma_(z[4], l2, s);
+  R = R + abs_(s);
+  s = fma_(z[5], l3, s);
+  R = R + abs_(s);
+  s = fma_(z[6], l4, s);
+  R = R + abs_(s);
+  const float det = p + s;
+  constexpr float u = (float)Eps<float>::u;
+  constexpr float eta64 = (float)(64.0 * Eps<float>::eta);
+  const float bound = (1.0f + 64.0f * u) * fma_(eta64, 1.0f + X, u * ((abs_(det) + R) + C));
   if (bound_out) *bound_out = bound;
+  forget_all(z);
+  dot3<float, true>(z[0], z[2], -z[5], z[5], -z[6], z[6], unused, &ordered);
+  const DW<float> c2 = dot3<float, true>(z[0], z[1], -z[3], z[3], -z[4], z[4], unused, &ordered);
   const float t = 1.0f / det;
-  const bool ok = ordered && det > 0.0f && finite_(det) && finite_(t) && !(bound > REROUTE_REL * det) &&
-                  z[0] > 0.0f && c[2].hi + c[2].lo > 0.0f;
-  scale_comp(c, t, x);
-  return ok;
+  return ordered && det > 0.0f && finite_(det) && finite_(t) && !(bound > REROUTE_REL * det) && z[0] > 0.0f &&
+         c2.hi + c2.lo > 0.0f;
+}
+
+// adjugate_comp_quick: the plain FP64 evaluation, rounded to FP32, and what
+// it settles.  With h = a d f, tr = a + d + f, for positive a, 2x2 minors and
+// det, tr <= 2^40 and det >= 2^-88 (1 + tr):
+// * h <= 2^24 det: QUICK_VALUE, the result stands.  With u = 2^-53: the
+//   minors give |e|^2 <= d f and so on, so the products of the cofactors of
+//   row 0 have magnitude sums S_i with M = sum |x_i| S_i <= (4 + 2 sqrt 2) h
+//   < 6.84 h (x = a, Re b, Im b, Re c, Im c; Cauchy-Schwarz for the two parts
+//   of b and of c).  The products are exact, so det is off by at most
+//   7 u M <= 9e-8 det, and each cofactor by 2 u S, 2^-27 of the largest.
+//   (Largest error found on 600,000 matrices up to h = 2^24 det, of det and of
+//   the inverse: 6.0e-8 and 5.6e-8, as of the error-free form, which is what
+//   the rounding to FP32 alone leaves.)  The pixel is positive definite:
+//   a det = c1 c2 - |e_c|^2 (c1, c2 the cofactors of d and f), so no minor whose
+//   computed value is positive can be negative; its status is ST_OK or
+//   ST_REROUTED.
+// * h <= 2^18 det: QUICK_ALL, its status is ST_OK.  By Fischer's inequality
+//   each minor is at least 2^-18 of its product of diagonal entries, 64 FP32
+//   roundings of it, so the FP32 evaluation finds its FastTwoSums ordered and
+//   its leading minor positive.  With u = 2^-24: its low words are sums of
+//   rounding errors, |t| and |s| of dot3 at most 2 u S and 3 u S, so
+//   rerr_i <= 8 u S_i; of det_comp, R <= 59 u M and C <= 8 u M; so its bound is
+//   E <= u det + 67 u^2 M + 65 eta (1 + X) with X <= 2.5 tr, at most
+//   (0.6 + 4.3 + 0.01) 1e-7 det: half of REROUTE_REL.  The range keeps every
+//   FP32 product below 2^121 and the diagonal products (each at least det
+//   over the third entry) above 2^-88.
+enum : int { QUICK_NONE = 0, QUICK_VALUE = 1, QUICK_ALL = 2 };
+
+PX_HD int adjugate_comp_quick(const float z[9], float x[9], float& det) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  const double a = z[0], d = z[1], f = z[2], br = z[3], bi = z[4], cr = z[5], ci = z[6], er = z[7], ei = z[8];
+  const double c0 = fma_(-ei, ei, fma_(-er, er, d * f));
+  const double c1 = fma_(-ci, ci, fma_(-cr, cr, a * f));
+  const double c2 = fma_(-bi, bi, fma_(-br, br, a * d));
+  const double c3 = fma_(-br, f, fma_(ci, ei, cr * er));
+  const double c4 = fma_(-bi, f, fma_(-cr, ei, ci * er));
+  const double c5 = fma_(-cr, d, fma_(-bi, ei, br * er));
+  const double c6 = fma_(-ci, d, fma_(bi, er, br * ei));
+  const double c7 = fma_(-a, er, fma_(ci, bi, cr * br));
+  const double c8 = fma_(-a, ei, fma_(-cr, bi, ci * br));
+  const double dd = fma_(ci, c6, fma_(cr, c5, fma_(bi, c4, fma_(br, c3, a * c0))));
+  const double t = 1.0 / dd;
+  det = (float)dd;
+  x[0] = (float)(c0 * t);
+  x[1] = (float)(c1 * t);
+  x[2] = (float)(c2 * t);
+  x[3] = (float)(c3 * t);
+  x[4] = (float)(c4 * t);
+  x[5] = (float)(c5 * t);
+  x[6] = (float)(c6 * t);
+  x[7] = (float)(c7 * t);
+  x[8] = (float)(c8 * t);
+  const float tr = z[0] + z[1] + z[2], h = z[0] * z[1] * z[2];
+  constexpr float lo = 3.2311742677852644e-27f;  // 2^-88
+  const bool ok = (z[0] > 0.0f) & (x[0] > 0.0f) & (x[1] > 0.0f) & (x[2] > 0.0f) & (tr <= 1099511627776.0f) &
+                  (det >= fma_(lo, tr, lo)) & (h <= 16777216.0f * det);
+  return !ok ? QUICK_NONE : h <= 262144.0f * det ? QUICK_ALL : QUICK_VALUE;
 }
 
 // Cofactors of an FP32 matrix in FP64.  A product of two FP32 numbers has at
@@ -347,10 +481,10 @@ PX_HD void cofactors_widened(const double z[9], DW<double> c[9]) {
   c[8] = sum3_plain(ci * br, -(cr * bi), -(a * ei));
 }
 
-// adjugate_comp_reroute: the FP64 recompute of one pixel, rounded to FP32:
-// exact-product cofactors as above, then the compensated determinant, the
-// one division and the scaling of the FP64 compensated form (plain for the
-// plainly summed cofactors).
+// adjugate_comp_reroute: the error-free FP64 evaluation of one pixel, rounded
+// to FP32: exact-product cofactors as above, then the compensated
+// determinant, the one division and the scaling of the FP64 compensated form
+// (plain for the plainly summed cofactors).
 PX_HD int adjugate_comp_reroute(const float z[9], float x[9], float& det) {
   double zd[9], xd[9], dd;
 #pragma unroll
@@ -379,9 +513,110 @@ PX_HD int adjugate_comp_reroute(const float z[9], float x[9], float& det) {
   return st;
 }
 
-PX_HD int adjugate_comp(const float z[9], float x[9], float& det, float* bound_out = nullptr) {
-  if (adjugate_comp_try(z, x, det, bound_out)) return ST_OK;
-  return adjugate_comp_reroute(z, x, det);
+// The same evaluation, bit for bit, with the cofactors formed one at a time,
+// once for the determinant and once to be scaled: a fifth more operations, 30
+// fewer registers, for kernels that keep much else in registers and come here
+// rarely.
+template <int K>
+PX_HD DW<double> cofactor_widened(const float z[9]) {
+  const double a = z[0], d = z[1], f = z[2], br = z[3], bi = z[4], cr = z[5], ci = z[6], er = z[7], ei = z[8];
+  if constexpr (K == 0) return sum3_exact(d * f, -(er * er), -(ei * ei));
+  else if constexpr (K == 1) return sum3_plain(a * f, -(cr * cr), -(ci * ci));
+  else if constexpr (K == 2) return sum3_exact(a * d, -(br * br), -(bi * bi));
+  else if constexpr (K == 3) return sum3_exact(cr * er, ci * ei, -(br * f));
+  else if constexpr (K == 4) return sum3_exact(ci * er, -(cr * ei), -(bi * f));
+  else if constexpr (K == 5) return sum3_exact(br * er, -(bi * ei), -(cr * d));
+  else if constexpr (K == 6) return sum3_exact(br * ei, bi * er, -(ci * d));
+  else if constexpr (K == 7) return sum3_plain(cr * br, ci * bi, -(a * er));
+  else return sum3_plain(ci * br, -(cr * bi), -(a * ei));
+}
+
+// One more term x c of the compensated determinant (p, s), c the cofactor K,
+// as det_comp adds it; returns c's low word, which det_comp adds later.
+template <int K>
+PX_HD double det_term(float (&z)[9], float x, double& p, double& s) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  forget_all(z);
+  const DW<double> c = cofactor_widened<K>(z);
+  const double h = (double)x * c.hi;
+  const double r = fma_((double)x, c.hi, -h);
+  double q;
+  two_sum(p, h, p, q);
+  s = s + (q + r);
+  return c.lo;
+}
+
+template <int K>
+PX_HD float scale_widened(float (&z)[9], double t) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  forget_all(z);
+  const DW<double> c = cofactor_widened<K>(z);
+  if constexpr (K == 1 || K >= 7) return (float)(c.hi * t);
+  else return (float)fma_(c.hi, t, c.lo * t);
+}
+
+PX_HD int adjugate_comp_reroute_small(const float z0[9], float x[9], float& det) {
+#if defined(__clang__)
+#pragma clang fp contract(off)
+#endif
+  float z[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) z[k] = z0[k];
+  double dd, minor;
+  {
+    const DW<double> c0 = cofactor_widened<0>(z);
+    double p = (double)z[0] * c0.hi, s = fma_((double)z[0], c0.hi, -p);
+    const double l0 = c0.lo;
+    const double l1 = det_term<3>(z, z[3], p, s), l2 = det_term<4>(z, z[4], p, s);
+    const double l3 = det_term<5>(z, z[5], p, s), l4 = det_term<6>(z, z[6], p, s);
+    s = fma_((double)z[6], l4,
+             fma_((double)z[5], l3, fma_((double)z[4], l2, fma_((double)z[3], l1, fma_((double)z[0], l0, s)))));
+    forget_all(z);
+    const DW<double> cm = cofactor_widened<2>(z);
+    dd = p + s;
+    minor = cm.hi + cm.lo;
+  }
+  const double t = 1.0 / dd;
+  int st = classify(dd, t, (double)z[0], minor);
+  x[0] = scale_widened<0>(z, t);
+  x[1] = scale_widened<1>(z, t);
+  x[2] = scale_widened<2>(z, t);
+  x[3] = scale_widened<3>(z, t);
+  x[4] = scale_widened<4>(z, t);
+  x[5] = scale_widened<5>(z, t);
+  x[6] = scale_widened<6>(z, t);
+  x[7] = scale_widened<7>(z, t);
+  x[8] = scale_widened<8>(z, t);
+  det = (float)dd;
+  if (st == ST_OK) {
+    st = classify(det, 1.0f / det, z0[0], 1.0f);
+    if (st == ST_OK) st = ST_REROUTED;
+  }
+  return st;
+}
+
+// What adjugate_comp_quick left over of a pixel (quick: what it returned, not
+// QUICK_ALL).  want_st: the status is used; ST_OK is returned otherwise.
+PX_HD int adjugate_comp_rest(const float z[9], float x[9], float& det, int quick, bool want_st) {
+  int st = ST_REROUTED;
+  if (quick == QUICK_NONE) st = adjugate_comp_reroute_small(z, x, det);
+  if (!want_st || adjugate_comp_try(z)) st = ST_OK;
+  return st;
+}
+
+PX_HD int adjugate_comp(const float z[9], float x[9], float& det, bool want_st) {
+  const int quick = adjugate_comp_quick(z, x, det);
+  return quick == QUICK_ALL ? ST_OK : adjugate_comp_rest(z, x, det, quick, want_st);
+}
+
+// The same with the bound of the compensated FP32 evaluation.
+PX_HD int adjugate_comp(const float z[9], float x[9], float& det, float* bound_out) {
+  adjugate_comp_try(z, bound_out);
+  return adjugate_comp(z, x, det, true);
 }
 
 // ---------------------------------------------------------------------------

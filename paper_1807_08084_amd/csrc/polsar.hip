@@ -9,7 +9,7 @@
 // stores.  Pixels are independent; lanes share only the fixed-order
 // reductions of the Wishart sum, the status counters, and the wave's LDS
 // queue of FP32 pixels recomputed in FP64.  This file also holds the fused
-// multilook (per-pixel looks, and the spatial boxcar form), block-diagonal
+// multilook (per-pixel looks), block-diagonal
 // and out-of-core streaming entry points.
 #include <hip/hip_runtime.h>
 
@@ -23,9 +23,11 @@
 
 #include "../../include/polsar.h"
 #include "common.hpp"
+#include "host.hpp"
 
 namespace {
 using namespace polsar_dev;
+using namespace polsar_host;
 
 struct InvDetArgs {
   const void* z;
@@ -38,6 +40,7 @@ struct InvDetArgs {
   int64_t n;      // pixels
   int64_t nvec;   // full vectors: n / V
   int64_t tiles;  // ceil(nvec / (block * U)), at least 1
+  int64_t tail;   // the block of the last tile: it takes the n mod V pixels after the last full vector
 };
 
 // Stores of one pixel-vector's results.
@@ -70,7 +73,7 @@ __device__ __forceinline__ void inv_det_vec(const InvDetArgs& a, const T (&in)[9
     T zz[9], xx[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) zz[k] = in[k][l];
-    st[l] = run_pixel<T, OP>(zz, xx, dt[l]);
+    st[l] = run_pixel<T, OP>(zz, xx, dt[l], a.status || a.counters);
 #pragma unroll
     for (int k = 0; k < 9; ++k) out[k][l] = xx[k];
     tally(st[l], c0, c1, c2);
@@ -79,7 +82,7 @@ __device__ __forceinline__ void inv_det_vec(const InvDetArgs& a, const T (&in)[9
 }
 
 template <class T, int OP, int V, int U, bool NT>
-__global__ __launch_bounds__(256) void k_inv_det(InvDetArgs a) {
+__global__ __launch_bounds__(256, OP == ADJ_COMP && U == 1 ? 4 : 1) void k_inv_det(InvDetArgs a) {
   const T* __restrict__ z = (const T*)a.z;
   const int B = blockDim.x;
   unsigned c0 = 0, c1 = 0, c2 = 0;
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(256) void k_inv_det(InvDetArgs a) {
       };
       float out[U][9][V], dt[U][V];
       int st[U][V];
-      comp_f32_wave<U, V>(load, valid, out, dt, st, q, qs);
+      comp_f32_wave<U, V>(load, valid, out, dt, st, q, qs, a.status || a.counters);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (!valid[u]) continue;
@@ -124,21 +127,22 @@ __global__ __launch_bounds__(256) void k_inv_det(InvDetArgs a) {
         if (v < a.nvec) inv_det_vec<T, OP, V, NT>(a, in[u], v, c0, c1, c2);
       }
     }
-    if (V > 1 && tile == a.tiles - 1) {
-      // the n mod V pixels after the last full vector, one per lane
-      const int64_t i = a.nvec * V + threadIdx.x;
-      if (i < a.n) {
-        T zz[9], xx[9], dt;
+  }
+  // after the loop: inside it, the compiler keeps its addresses and constants
+  // in registers across the tiles (172 registers instead of 118 at V = 2)
+  if (V > 1 && blockIdx.x == a.tail) {
+    const int64_t i = a.nvec * V + threadIdx.x;
+    if (i < a.n) {
+      T zz[9], xx[9], dt;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) zz[k] = z[k * a.zp + i];
-        const int st = run_pixel<T, OP>(zz, xx, dt);
-        tally(st, c0, c1, c2);
-        if (a.inv)
+      for (int k = 0; k < 9; ++k) zz[k] = z[k * a.zp + i];
+      const int st = run_pixel<T, OP>(zz, xx, dt, a.status || a.counters);
+      tally(st, c0, c1, c2);
+      if (a.inv)
 #pragma unroll
-          for (int k = 0; k < 9; ++k) ((T*)a.inv)[k * a.ip + i] = xx[k];
-        if (a.det) ((T*)a.det)[i] = dt;
-        if (a.status) a.status[i] = (uint8_t)st;
-      }
+        for (int k = 0; k < 9; ++k) ((T*)a.inv)[k * a.ip + i] = xx[k];
+      if (a.det) ((T*)a.det)[i] = dt;
+      if (a.status) a.status[i] = (uint8_t)st;
     }
   }
   if (a.counters) flush_counters(a.counters, c0, c1, c2);
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(256) void k_multilook(MultilookArgs a) {
         };
         float out[1][9][V], dt[1][V];
         int st[1][V];
-        comp_f32_wave<1, V>(load, valid, out, dt, st, q, qs);
+        comp_f32_wave<1, V>(load, valid, out, dt, st, q, qs, a.o.status || a.o.counters);
 #pragma unroll
         for (int l = 0; l < V; ++l) tally(st[0][l], c0, c1, c2);
         store_vec<T, V, NT>(a.o, out[0], dt[0], st[0], v);
@@ -218,263 +222,33 @@ __global__ __launch_bounds__(256) void k_multilook(MultilookArgs a) {
         inv_det_vec<T, OP, V, NT>(a.o, zz, v, c0, c1, c2);
       }
     }
-    if (V > 1 && tile == a.o.tiles - 1) {
-      const int64_t i = a.o.nvec * V + threadIdx.x;
-      if (i < a.o.n) {
-        double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int look = 0; look < a.n_looks; ++look) {
-          T s6[6];
+  }
+  if (V > 1 && blockIdx.x == a.o.tail) {
+    const int64_t i = a.o.nvec * V + threadIdx.x;
+    if (i < a.o.n) {
+      double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+      for (int look = 0; look < a.n_looks; ++look) {
+        T s6[6];
 #pragma unroll
-          for (int j = 0; j < 6; ++j) s6[j] = S[(int64_t)(6 * look + j) * a.lp + i];
-          px::look_accumulate(s6, acc);
-        }
-        T zz[9], xx[9], dt;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) zz[k] = (T)(acc[k] * inv_n);
-        if (a.z)
-#pragma unroll
-          for (int k = 0; k < 9; ++k) ((T*)a.z)[k * a.zp + i] = zz[k];
-        const int st = run_pixel<T, OP>(zz, xx, dt);
-        tally(st, c0, c1, c2);
-        if (a.o.inv)
-#pragma unroll
-          for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[k * a.o.ip + i] = xx[k];
-        if (a.o.det) ((T*)a.o.det)[i] = dt;
-        if (a.o.status) a.o.status[i] = (uint8_t)st;
+        for (int j = 0; j < 6; ++j) s6[j] = S[(int64_t)(6 * look + j) * a.lp + i];
+        px::look_accumulate(s6, acc);
       }
+      T zz[9], xx[9], dt;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) zz[k] = (T)(acc[k] * inv_n);
+      if (a.z)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ((T*)a.z)[k * a.zp + i] = zz[k];
+      const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
+      tally(st, c0, c1, c2);
+      if (a.o.inv)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[k * a.o.ip + i] = xx[k];
+      if (a.o.det) ((T*)a.o.det)[i] = dt;
+      if (a.o.status) a.o.status[i] = (uint8_t)st;
     }
   }
   if (a.o.counters) flush_counters(a.o.counters, c0, c1, c2);
-}
-
-// ------------------------------------------------------------------ boxcar multilook
-// Spatial multilook fused with the inverse: Eq. (ZN) with the looks of pixel
-// (y, x) taken from its (2R+1) x (2R+1) neighbourhood in a single-look
-// image, clipped at the border,
-//   Z(y, x) = (1/|W|) sum_{(y', x') in W(y, x)} S(y', x') S(y', x')^H.
-// A block (one wave) owns BOX_TW output columns of a strip of box_strip(R)
-// rows and walks down it one input row at a time: the row's single-look
-// pixels (with an R-pixel halo each side, zeros outside the image, which add
-// nothing) are staged in LDS in FP64, double-buffered, while the next row is
-// being loaded; each lane forms the sum of its K = 2R+1 horizontal
-// neighbours' outer products in FP64 (exact products for FP32 input) and
-// adds K consecutive row sums for its output.  Each output is scaled by the
-// reciprocal of the clipped window size (within an FP64 ulp of the
-// quotient), rounded to the storage type (optionally stored) and inverted
-// with the per-pixel function of the per-call kernel.
-//
-// The vertical sums, without subtraction (so every window keeps the error
-// bound of a plain sum of its own terms), two ways:
-// * K <= 5 (k_boxcar_shift): the last K row sums sit in registers, oldest
-//   first, shifted down one slot per row, and the K of a window are added
-//   in ascending row order.
-// * K = 7 (k_boxcar_grouped): rows are taken in groups of K, row j of a
-//   group going to slot j (the loop over a group is unrolled, so slot
-//   indices are compile-time constants and nothing is shifted).  The window
-//   that ends at row j of a group is the previous group's rows j+1 .. K-1
-//   plus this group's rows 0 .. j: a running prefix sum of this group plus
-//   the previous group's suffix sum from row j+1, which the slots hold once
-//   a group ends and its suffix sums are formed in place (the scheme of van
-//   Herk, and of Gil and Werman, for running maxima, with + for max): about
-//   three additions of nine components per output for any K, instead of
-//   K-1 plus the shift (7x7 on a 4096^2 image: 44.6-45.3 against 41.6
-//   Gpx/s).  The group's K inlined inverses need more registers than the
-//   shifted ring's one: at K = 3 and 5 they spilled and ran 25-35% slower.
-constexpr int BOX_TW = 64, BOX_MAX_R = 3;
-// Strip height: each strip re-forms the row sums of its 2R halo rows, so
-// wide windows take taller strips (7x7: 64 rows 4% faster than 32); 3x3
-// keeps 32 (64 rows, half the blocks, 5% slower).
-constexpr int box_strip(int R) { return R >= 2 ? 64 : 32; }
-
-struct BoxArgs {
-  const void* s;
-  int64_t sp;
-  void* z;
-  int64_t zp;
-  void* inv;
-  int64_t ip;
-  void* det;
-  uint8_t* status;
-  unsigned long long* counters;
-  int64_t H, W;
-  int64_t nbx;  // blocks across the image
-};
-
-// The block's strip and this lane's column.
-template <int R>
-struct BoxStrip {
-  int64_t x0, ys, y_first, y_last, gx, cols;
-  __device__ BoxStrip(const BoxArgs& a) {
-    const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t bx = t % a.nbx, by = t / a.nbx;
-    x0 = bx * BOX_TW;
-    ys = by * box_strip(R);
-    const int64_t ye = ys + box_strip(R) < a.H ? ys + box_strip(R) : a.H;
-    y_first = ys - R;  // rows staged (outside the image: zeros)
-    y_last = ye - 1 + R;
-    gx = x0 + threadIdx.x;
-    cols = (gx + R < a.W ? gx + R : a.W - 1) - (gx - R > 0 ? gx - R : 0) + 1;
-  }
-};
-
-// The staged pixels of input row y this lane loads.  Pixels outside the
-// image load pixel 0 instead (every load is in bounds and unconditional, so
-// the loads stay in flight while the current row is summed) and are staged
-// as zeros, which add nothing.
-template <class T, int R, int P>
-__device__ __forceinline__ void box_load_row(const BoxArgs& a, int64_t x0, int64_t y, T (&v)[P][6], bool (&ok)[P]) {
-  constexpr int SW = BOX_TW + 2 * R;
-  const T* __restrict__ S = (const T*)a.s;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const int col = threadIdx.x + p * BOX_TW;
-    const int64_t x = x0 - R + col;
-    ok[p] = col < SW && y >= 0 && y < a.H && x >= 0 && x < a.W;
-    const int64_t i = ok[p] ? y * a.W + x : 0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) v[p][k] = S[k * a.sp + i];
-  }
-}
-
-// Stage the loaded row in an LDS row buffer, in FP64.
-template <class T, int R, int P>
-__device__ __forceinline__ void box_stage(double (*row)[BOX_TW + 2 * R], const T (&v)[P][6], const bool (&ok)[P]) {
-  constexpr int SW = BOX_TW + 2 * R;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const int col = threadIdx.x + p * BOX_TW;
-    if (col < SW)
-#pragma unroll
-      for (int k = 0; k < 6; ++k) row[k][col] = ok[p] ? (double)v[p][k] : 0.0;
-  }
-}
-
-// This lane's row sum of the staged row: its K horizontal neighbours.
-template <int R>
-__device__ __forceinline__ void box_row_sum(double (*row)[BOX_TW + 2 * R], double (&sum)[9]) {
-  double s6[6];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) s6[k] = row[k][threadIdx.x];
-  px::look_first(s6, sum);
-#pragma unroll
-  for (int dx = 1; dx < 2 * R + 1; ++dx) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) s6[k] = row[k][threadIdx.x + dx];
-    px::look_accumulate_chained(s6, sum);
-  }
-}
-
-// Output row yo of this lane from its window sum: Z, inverse, det, status.
-template <class T, int OP, int R>
-__device__ __forceinline__ void box_output(const BoxArgs& a, const BoxStrip<R>& b, int64_t yo, const double (&w)[9],
-                                           unsigned& c0, unsigned& c1, unsigned& c2) {
-  const int64_t rows = (yo + R < a.H ? yo + R : a.H - 1) - (yo - R > 0 ? yo - R : 0) + 1;
-  const double rcp = 1.0 / (double)(rows * b.cols);
-  T zz[9], xx[9], dt;
-#pragma unroll
-  for (int c = 0; c < 9; ++c) zz[c] = (T)(w[c] * rcp);
-  const int64_t i = yo * a.W + b.gx;
-  if (a.z)
-#pragma unroll
-    for (int c = 0; c < 9; ++c) ((T*)a.z)[c * a.zp + i] = zz[c];
-  const int st_px = run_pixel<T, OP>(zz, xx, dt);
-  tally(st_px, c0, c1, c2);
-  if (a.inv)
-#pragma unroll
-    for (int c = 0; c < 9; ++c) ((T*)a.inv)[c * a.ip + i] = xx[c];
-  if (a.det) ((T*)a.det)[i] = dt;
-  if (a.status) a.status[i] = (uint8_t)st_px;
-}
-
-template <class T, int OP, int R>
-__global__ __launch_bounds__(BOX_TW) void k_boxcar_shift(BoxArgs a) {
-  constexpr int K = 2 * R + 1, SW = BOX_TW + 2 * R;
-  constexpr int P = (SW + BOX_TW - 1) / BOX_TW;  // staged pixels per lane and row
-  __shared__ double row[2][6][SW];
-  const BoxStrip<R> b(a);
-  double ring[K][9];  // row sums of rows y - 2R .. y, oldest first
-#pragma unroll
-  for (int m = 0; m < K; ++m)
-#pragma unroll
-    for (int c = 0; c < 9; ++c) ring[m][c] = 0.0;
-  T pre[P][6];
-  bool pok[P];
-  unsigned c0 = 0, c1 = 0, c2 = 0;
-  box_load_row<T, R, P>(a, b.x0, b.y_first, pre, pok);
-#pragma unroll 1
-  for (int64_t y = b.y_first; y <= b.y_last; ++y) {  // the same for every lane of the block
-    const int buf = (int)((y - b.y_first) & 1);
-    box_stage<T, R, P>(row[buf], pre, pok);
-    __syncthreads();
-    if (y + 1 <= b.y_last) box_load_row<T, R, P>(a, b.x0, y + 1, pre, pok);  // in flight while this row is summed
-#pragma unroll
-    for (int m = 0; m + 1 < K; ++m)
-#pragma unroll
-      for (int c = 0; c < 9; ++c) ring[m][c] = ring[m + 1][c];
-    box_row_sum<R>(row[buf], ring[K - 1]);
-    // output row y - R, whose window rows y - 2R .. y the ring now holds
-    const int64_t yo = y - R;
-    if (yo >= b.ys && b.gx < a.W) {
-      double w[9];
-#pragma unroll
-      for (int c = 0; c < 9; ++c) w[c] = ring[0][c];
-#pragma unroll
-      for (int m = 1; m < K; ++m)
-#pragma unroll
-        for (int c = 0; c < 9; ++c) w[c] += ring[m][c];
-      box_output<T, OP, R>(a, b, yo, w, c0, c1, c2);
-    }
-  }
-  if (a.counters) flush_counters(a.counters, c0, c1, c2);
-}
-
-template <class T, int OP, int R>
-__global__ __launch_bounds__(BOX_TW) void k_boxcar_grouped(BoxArgs a) {
-  constexpr int K = 2 * R + 1, SW = BOX_TW + 2 * R;
-  constexpr int P = (SW + BOX_TW - 1) / BOX_TW;
-  __shared__ double row[2][6][SW];
-  const BoxStrip<R> b(a);
-  // slot j: the row sum of row j of the current group, or, once the group is
-  // done, the sum of its rows j .. K-1
-  double ring[K][9];
-#pragma unroll
-  for (int m = 0; m < K; ++m)
-#pragma unroll
-    for (int c = 0; c < 9; ++c) ring[m][c] = 0.0;
-  T pre[P][6];
-  bool pok[P];
-  unsigned c0 = 0, c1 = 0, c2 = 0;
-  box_load_row<T, R, P>(a, b.x0, b.y_first, pre, pok);
-#pragma unroll 1
-  for (int64_t y0 = b.y_first; y0 <= b.y_last; y0 += K) {  // the same for every lane of the block
-    double run[9];  // prefix sum of the group's row sums
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int64_t y = y0 + j;
-      if (y > b.y_last) break;
-      const int buf = (int)((y - b.y_first) & 1);
-      box_stage<T, R, P>(row[buf], pre, pok);
-      __syncthreads();
-      if (y + 1 <= b.y_last) box_load_row<T, R, P>(a, b.x0, y + 1, pre, pok);
-      box_row_sum<R>(row[buf], ring[j]);
-#pragma unroll
-      for (int c = 0; c < 9; ++c) run[c] = j == 0 ? ring[0][c] : run[c] + ring[j][c];
-      // output row y - R: window rows y - 2R .. y
-      const int64_t yo = y - R;
-      if (yo >= b.ys && b.gx < a.W) {
-        double w[9];
-#pragma unroll
-        for (int c = 0; c < 9; ++c) w[c] = j + 1 < K ? ring[j + 1 < K ? j + 1 : 0][c] + run[c] : run[c];
-        box_output<T, OP, R>(a, b, yo, w, c0, c1, c2);
-      }
-    }
-    // the group's suffix sums, for the next group's windows
-#pragma unroll
-    for (int j = K - 2; j >= 0; --j)
-#pragma unroll
-      for (int c = 0; c < 9; ++c) ring[j][c] += ring[j + 1][c];
-  }
-  if (a.counters) flush_counters(a.counters, c0, c1, c2);
 }
 
 // ------------------------------------------------------------------ block diagonal
@@ -509,7 +283,7 @@ __global__ __launch_bounds__(256) void k_blockdiag(BlockArgs a) {
           T zz[9], xx[9];
 #pragma unroll
           for (int k = 0; k < 9; ++k) zz[k] = in[k][l];
-          const int st = run_pixel<T, OP>(zz, xx, dt[l]);
+          const int st = run_pixel<T, OP>(zz, xx, dt[l], a.o.status || a.o.counters);
 #pragma unroll
           for (int k = 0; k < 9; ++k) out[k][l] = xx[k];
           prod[l] *= dt[l];
@@ -525,27 +299,27 @@ __global__ __launch_bounds__(256) void k_blockdiag(BlockArgs a) {
       if (a.o.det) store_v<T, V, NT>((T*)a.o.det + v * V, prod);
       if (a.o.status) store_status<V>(a.o.status + v * V, worst);
     }
-    if (V > 1 && tile == a.o.tiles - 1) {
-      const int64_t i = a.o.nvec * V + threadIdx.x;
-      if (i < a.o.n) {
-        T prod = T(1);
-        int worst = 0;
-        for (int b = 0; b < a.k; ++b) {
-          T zz[9], xx[9], dt;
+  }
+  if (V > 1 && blockIdx.x == a.o.tail) {
+    const int64_t i = a.o.nvec * V + threadIdx.x;
+    if (i < a.o.n) {
+      T prod = T(1);
+      int worst = 0;
+      for (int b = 0; b < a.k; ++b) {
+        T zz[9], xx[9], dt;
 #pragma unroll
-          for (int k = 0; k < 9; ++k) zz[k] = Z[(int64_t)(9 * b + k) * a.o.zp + i];
-          const int st = run_pixel<T, OP>(zz, xx, dt);
-          prod *= dt;
-          worst = st > worst ? st : worst;
-          if (a.o.inv)
+        for (int k = 0; k < 9; ++k) zz[k] = Z[(int64_t)(9 * b + k) * a.o.zp + i];
+        const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
+        prod *= dt;
+        worst = st > worst ? st : worst;
+        if (a.o.inv)
 #pragma unroll
-            for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[(int64_t)(9 * b + k) * a.o.ip + i] = xx[k];
-          if (a.bdet) ((T*)a.bdet)[(int64_t)b * a.bp + i] = dt;
-        }
-        tally(worst, c0, c1, c2);
-        if (a.o.det) ((T*)a.o.det)[i] = prod;
-        if (a.o.status) a.o.status[i] = (uint8_t)worst;
+          for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[(int64_t)(9 * b + k) * a.o.ip + i] = xx[k];
+        if (a.bdet) ((T*)a.bdet)[(int64_t)b * a.bp + i] = dt;
       }
+      tally(worst, c0, c1, c2);
+      if (a.o.det) ((T*)a.o.det)[i] = prod;
+      if (a.o.status) a.o.status[i] = (uint8_t)worst;
     }
   }
   if (a.o.counters) flush_counters(a.o.counters, c0, c1, c2);
@@ -712,13 +486,11 @@ std::map<std::tuple<int, int, int, int>, polsar_launch> g_cfg;
 // 9-16% faster than the 4096x4096 image's shape, which is 4% faster there.
 constexpr int64_t WISHART_SMALL = int64_t(1) << 23;
 // Images of at least this many pixels take the inverse kernel's launch from
-// op 6 of the table instead of op 0.  On an 8192x8192 image whose pixels are
-// a fifth recomputed in FP64 the FP32 compensated kernel with 8-byte
-// accesses ran 15% below its best shape (16-byte accesses in 128-lane
-// blocks, at most 8 per CU: four pixels per lane fill the wave's FP64 queue
-// twice as well as two), which stays within 3-5% of the best on an
-// 8192x8192 image with almost no recomputes; on 4096x4096 images 8-byte
-// accesses are 2-5% faster.  The Cholesky forms and the FP32-I/O FP64
+// op 6 of the table instead of op 0.  FP32 compensated on 8192x8192: 16-byte
+// accesses in 128-lane blocks, at most 4 per CU: 846 us with a quarter of the
+// pixels past the quick form, 841 with almost none (8-byte accesses, at most 6
+// per CU: 866 and 845; on 4096x4096 images those take 204 us against 209).
+// The Cholesky forms and the FP32-I/O FP64
 // adjugate take the joint best of both 8192x8192 images (1-2% over their
 // op-0 shapes); the other forms keep their op-0 shapes.
 constexpr int64_t INV_DET_LARGE = int64_t(1) << 25;
@@ -733,9 +505,9 @@ polsar_launch default_launch(int op, int dtype, int method, int prec) {
     case 5:  // the Wishart kernel below WISHART_SMALL pixels: more, smaller tiles (FP64 on 2048^2: 5 blocks
              // per CU 0.757 of HBM, the Wishart tuner's pick in every bench run, against 0.689 with 4)
       return f64 ? polsar_launch{128, 1, 0, 1, 8, 5} : polsar_launch{128, 1, 0, 1, 8, 5};
-    case 2:  // FP32 compensated: 8-byte accesses, at most 8 blocks of 256 lanes per CU (0.75 of HBM on the
-             // four-look 4096x4096 image against 0.67 with 16-byte accesses and no cap)
-      if (!f64 && !chol && prec == POLSAR_COMPENSATED) return polsar_launch{256, 1, 0, 1, 8, 8};
+    case 2:  // FP32 compensated: 8-byte accesses, at most 6 blocks of 128 lanes per CU (four-look 4096x4096
+             // image: 357 us, 370 with 8 blocks of 256 lanes)
+      if (!f64 && !chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 8, 6};
       return f64 ? polsar_launch{256, 1, 0, 1, 8, 4} : polsar_launch{128, 1, 0, 1, 16, 0};
     case 3:  // FP32: one block of 128 lanes per tile, 8-byte accesses (64-image batch: 0.72 of HBM, against
              // 0.67 for the best persistent grid, 2 blocks of 256 lanes per CU)
@@ -744,7 +516,7 @@ polsar_launch default_launch(int op, int dtype, int method, int prec) {
       return polsar_launch{64, 1, 0, 1, 16, 5};
     case 6:  // the inverse kernel on images of at least INV_DET_LARGE pixels
       if (f64) break;
-      if (!chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 16, 8};
+      if (!chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 16, 4};
       if (!chol && prec == POLSAR_WIDE) return polsar_launch{64, 1, 0, 1, 16, 5};
       if (chol && prec == POLSAR_PLAIN) return polsar_launch{128, 1, 0, 1, 16, 3};
       if (chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 16, 8};
@@ -753,13 +525,12 @@ polsar_launch default_launch(int op, int dtype, int method, int prec) {
       break;
   }
   // op 0: winners of the autotuner on 4096x4096 and 8192x8192 images of the
-  // same recipe, taken together.  For FP32 compensated the 8-byte access
-  // with three waves per SIMD also keeps pixels recomputed in FP64 cheap
-  // (images with many of them run best with 16-byte access at the same
-  // occupancy, which streams the rest slower).  The FP64 adjugate runs 11%
+  // same recipe, taken together.  FP32 compensated, 4096x4096: 204-207 us with
+  // at most 6 blocks of 128 lanes of 8-byte accesses, without and with
+  // statuses, 210 and 211 with 8.  The FP64 adjugate runs 11%
   // faster on 8192x8192 with 16-byte accesses and 6 single-wave blocks per
   // CU than with 12 waves of 8-byte accesses (1% slower on 4096x4096).
-  if (!chol && prec == POLSAR_COMPENSATED) return f64 ? polsar_launch{64, 1, 0, 1, 16, 6} : polsar_launch{128, 1, 0, 1, 8, 8};
+  if (!chol && prec == POLSAR_COMPENSATED) return f64 ? polsar_launch{64, 1, 0, 1, 16, 6} : polsar_launch{128, 1, 0, 1, 8, 6};
   if (chol && prec == POLSAR_PLAIN) return f64 ? polsar_launch{64, 1, 0, 1, 16, 5} : polsar_launch{256, 1, 0, 1, 8, 3};
   if (!chol && prec == POLSAR_PLAIN) return f64 ? polsar_launch{64, 1, 0, 1, 16, 6} : polsar_launch{64, 1, 0, 1, 16, 5};
   if (chol && prec == POLSAR_WIDE) return polsar_launch{64, 2, 0, 1, 16, 0};
@@ -793,6 +564,19 @@ polsar_launch get_cfg(int op, int dtype, int method, int prec) {
   std::lock_guard<std::mutex> g(g_mu);
   auto it = g_cfg.find(std::make_tuple(op, dtype, method, prec));
   return it == g_cfg.end() ? default_launch(op, dtype, method, prec) : it->second;
+}
+
+// The inverse's launch.  An FP32 compensated call on a large image that wants
+// statuses (op 6) runs twice the resident blocks of the table: the FP32
+// evaluations of its ill-conditioned pixels need the waves (8192x8192 with
+// eigenvalues down to 1e-8: 858 us at 8 blocks per CU, 915 at 5), without
+// them fewer stream better (846 us at 4, 912 at 8).
+polsar_launch inv_det_cfg(int64_t n, int dtype, int method, int prec, bool want_st) {
+  const int op = polsar_inv_det_launch_op(n);
+  polsar_launch c = get_cfg(op, dtype, method, prec);
+  if (op == 6 && want_st && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED)
+    c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
+  return c;
 }
 
 bool valid_launch(const polsar_launch& c, int op) {
@@ -831,34 +615,6 @@ int64_t launch_grid(const polsar_launch& c, int64_t tiles, bool counters) {
   return grid;
 }
 
-inline size_t esize(int dtype) { return dtype == POLSAR_F64 ? 8 : 4; }
-
-// Byte range [lo, hi) spanned by `planes` planes of n elements at `pitch`.
-struct Range {
-  uintptr_t lo, hi;
-};
-Range span(const void* p, int planes, int64_t pitch, int64_t n, size_t es) {
-  uintptr_t lo = (uintptr_t)p;
-  return Range{lo, lo + (uintptr_t)(((planes - 1) * pitch + n) * (int64_t)es)};
-}
-bool overlap(Range a, Range b) { return a.lo < b.hi && b.lo < a.hi; }
-
-int check_planes(const void* p, int64_t pitch, int64_t n, size_t es) {
-  if (!p) return n == 0 ? POLSAR_OK : POLSAR_E_ARG;  // an empty batch may pass null planes
-  if (pitch < n || pitch > ((int64_t)1 << 40)) return POLSAR_E_ARG;
-  if ((uintptr_t)p % es) return POLSAR_E_ALIGN;
-  return POLSAR_OK;
-}
-
-bool vec_ok(const void* p, int64_t pitch, size_t es) {
-  return p == nullptr || (((uintptr_t)p % 16) == 0 && ((pitch * (int64_t)es) % 16) == 0);
-}
-
-int op_code(int method, int prec) {
-  if (method == POLSAR_ADJUGATE) return prec == POLSAR_PLAIN ? ADJ_PLAIN : prec == POLSAR_COMPENSATED ? ADJ_COMP : ADJ_WIDE;
-  return prec == POLSAR_PLAIN ? CHOL_PLAIN : prec == POLSAR_COMPENSATED ? CHOL_COMP : CHOL_WIDE;
-}
-
 // Launch helpers: pick the template instance for (V, U, NT).
 template <class T, int OP, int V, int U>
 hipError_t go_inv_det(const polsar_launch& c, int64_t grid, InvDetArgs& a, hipStream_t s) {
@@ -891,6 +647,7 @@ hipError_t dispatch_inv_det_v(const polsar_launch& c, InvDetArgs& a, hipStream_t
   const int64_t per_tile = (int64_t)c.block * unroll;
   a.tiles = std::max<int64_t>(1, (a.nvec + per_tile - 1) / per_tile);
   const int64_t grid = launch_grid(c, a.tiles, a.counters != nullptr);
+  a.tail = (a.tiles - 1) % grid;
   if (unroll == 1) return go_inv_det<T, OP, V, 1>(c, grid, a, s);
   if constexpr (OP == ADJ_COMP && std::is_same<T, float>::value) {
     return go_inv_det<T, OP, V, 2>(c, grid, a, s);
@@ -930,16 +687,6 @@ hipError_t launch_inv_det(int dtype, int op, const polsar_launch& c, bool vec, I
 }
 
 // Validates polsar_inv_det arguments; fills `a` and `vec` on success.
-// Valid (dtype, method, precision) combination?
-int check_mode(int dtype, int method, int prec) {
-  if (dtype != POLSAR_F32 && dtype != POLSAR_F64) return POLSAR_E_ARG;
-  if (method != POLSAR_ADJUGATE && method != POLSAR_CHOLESKY) return POLSAR_E_ARG;
-  if (prec != POLSAR_PLAIN && prec != POLSAR_COMPENSATED && prec != POLSAR_WIDE) return POLSAR_E_ARG;
-  if (dtype == POLSAR_F64 && prec == POLSAR_WIDE) return POLSAR_E_UNSUPPORTED;
-  if (dtype == POLSAR_F64 && method == POLSAR_CHOLESKY && prec != POLSAR_PLAIN) return POLSAR_E_UNSUPPORTED;
-  return POLSAR_OK;
-}
-
 int prepare_inv_det(int dtype, int method, int prec, int64_t n, const void* z, int64_t zp, void* inv,
                     int64_t ip, void* det, uint8_t* status, unsigned long long* counters, InvDetArgs& a,
                     bool& vec) {
@@ -969,7 +716,7 @@ int prepare_inv_det(int dtype, int method, int prec, int64_t n, const void* z, i
         return POLSAR_E_ALIAS;
     }
   }
-  a = InvDetArgs{z, zp, inv, ip, det, status, counters, n, 0, 0};
+  a = InvDetArgs{z, zp, inv, ip, det, status, counters, n, 0, 0, 0};
   const int VW = (int)(16 / es);
   vec = vec_ok(z, zp, es) && vec_ok(inv, ip, es) && vec_ok(det, 0, es) &&
         (status == nullptr || ((uintptr_t)status % VW) == 0);
@@ -982,6 +729,7 @@ hipError_t dispatch_multilook_v(const polsar_launch& c, MultilookArgs& a, hipStr
   a.o.nvec = a.o.n / V;
   a.o.tiles = std::max<int64_t>(1, (a.o.nvec + c.block - 1) / c.block);
   const int64_t grid = launch_grid(c, a.o.tiles, a.o.counters != nullptr);
+  a.o.tail = (a.o.tiles - 1) % grid;
   const size_t lds =
       launch_lds(c, (OP == ADJ_COMP && std::is_same<T, float>::value) ? comp_queue_bytes(c.block, V) : 0);
   if (c.nontemporal)
@@ -1017,54 +765,13 @@ hipError_t launch_multilook(int dtype, int op, const polsar_launch& c, bool vec,
   }
 }
 
-// ---- boxcar launch: one block (one wave) per BOX_TW columns x box_strip(R) rows,
-// a 1-D grid; the radius is a template parameter (the ring of row sums is
-// indexed at compile time)
-template <class T, int OP, int R>
-hipError_t go_boxcar_r(BoxArgs& a, hipStream_t s) {
-  a.nbx = (a.W + BOX_TW - 1) / BOX_TW;
-  const int64_t nby = (a.H + box_strip(R) - 1) / box_strip(R);
-  if constexpr (R <= 2)
-    hipLaunchKernelGGL((k_boxcar_shift<T, OP, R>), dim3((unsigned)(a.nbx * nby)), dim3(BOX_TW), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_boxcar_grouped<T, OP, R>), dim3((unsigned)(a.nbx * nby)), dim3(BOX_TW), 0, s, a);
-  return hipGetLastError();
-}
-
-template <class T, int OP>
-hipError_t go_boxcar(BoxArgs& a, int r, hipStream_t s) {
-  switch (r) {
-    case 0: return go_boxcar_r<T, OP, 0>(a, s);
-    case 1: return go_boxcar_r<T, OP, 1>(a, s);
-    case 2: return go_boxcar_r<T, OP, 2>(a, s);
-    default: return go_boxcar_r<T, OP, 3>(a, s);
-  }
-}
-
-hipError_t launch_boxcar(int dtype, int op, BoxArgs& a, int r, hipStream_t s) {
-  if (dtype == POLSAR_F32) {
-    switch (op) {
-      case ADJ_PLAIN: return go_boxcar<float, ADJ_PLAIN>(a, r, s);
-      case ADJ_COMP: return go_boxcar<float, ADJ_COMP>(a, r, s);
-      case ADJ_WIDE: return go_boxcar<float, ADJ_WIDE>(a, r, s);
-      case CHOL_PLAIN: return go_boxcar<float, CHOL_PLAIN>(a, r, s);
-      case CHOL_COMP: return go_boxcar<float, CHOL_COMP>(a, r, s);
-      default: return go_boxcar<float, CHOL_WIDE>(a, r, s);
-    }
-  }
-  switch (op) {
-    case ADJ_PLAIN: return go_boxcar<double, ADJ_PLAIN>(a, r, s);
-    case ADJ_COMP: return go_boxcar<double, ADJ_COMP>(a, r, s);
-    default: return go_boxcar<double, CHOL_PLAIN>(a, r, s);
-  }
-}
-
 // ---- block-diagonal launch
 template <class T, int OP, int V>
 hipError_t dispatch_block_v(const polsar_launch& c, BlockArgs& a, hipStream_t s) {
   a.o.nvec = a.o.n / V;
   a.o.tiles = std::max<int64_t>(1, (a.o.nvec + c.block - 1) / c.block);
   const int64_t grid = launch_grid(c, a.o.tiles, a.o.counters != nullptr);
+  a.o.tail = (a.o.tiles - 1) % grid;
   const size_t lds = launch_lds(c, 0);
   if (c.nontemporal)
     hipLaunchKernelGGL((k_blockdiag<T, OP, V, true>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
@@ -1200,7 +907,7 @@ int polsar_inv_det(int dtype, int method, int precision, int64_t n, const void* 
   int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, status, counters, a, vec);
   if (r) return r;
   if (n == 0) return POLSAR_OK;
-  const polsar_launch c = get_cfg(polsar_inv_det_launch_op(n), dtype, method, precision);
+  const polsar_launch c = inv_det_cfg(n, dtype, method, precision, status || counters);
   if (launch_inv_det(dtype, op_code(method, precision), c, vec, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
@@ -1232,47 +939,11 @@ int polsar_multilook_inv_det(int dtype, int method, int precision, int64_t n, in
   }
   if (n == 0) return POLSAR_OK;
   MultilookArgs a{looks, looks_pitch, n_looks, 1.0 / n_looks, z, z_pitch,
-                  InvDetArgs{nullptr, 0, inv, inv_pitch, det, status, counters, n, 0, 0}};
+                  InvDetArgs{nullptr, 0, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
   const bool vec = vec_ok(looks, looks_pitch, es) && vec_ok(z, z_pitch, es) && vec_ok(inv, inv_pitch, es) && vec_ok(det, 0, es) &&
         (status == nullptr || ((uintptr_t)status % (16 / es)) == 0);
   const polsar_launch c = get_cfg(2, dtype, method, precision);
   if (launch_multilook(dtype, op_code(method, precision), c, vec, a, (hipStream_t)stream) != hipSuccess)
-    return POLSAR_E_HIP;
-  return POLSAR_OK;
-}
-
-int polsar_boxcar_inv_det(int dtype, int method, int precision, int64_t height, int64_t width, int radius,
-                          const void* s, int64_t s_pitch, void* z, int64_t z_pitch, void* inv, int64_t inv_pitch,
-                          void* det, uint8_t* status, unsigned long long* counters, void* stream) {
-  int r = check_mode(dtype, method, precision);
-  if (r) return r;
-  if (height < 0 || width < 0 || radius < 0 || radius > BOX_MAX_R) return POLSAR_E_ARG;
-  if (height > ((int64_t)1 << 24) || width > ((int64_t)1 << 24)) return POLSAR_E_ARG;
-  const int64_t n = height * width;
-  // one block per 64 columns of a strip of 32 or 64 rows: at most ~2^21
-  // blocks, a 1-D grid
-  if (n > ((int64_t)1 << 32)) return POLSAR_E_ARG;
-  const size_t es = esize(dtype);
-  if ((r = check_planes(s, s_pitch, n, es))) return r;
-  if (z && (r = check_planes(z, z_pitch, n, es))) return r;
-  if (inv && (r = check_planes(inv, inv_pitch, n, es))) return r;
-  if (det && ((uintptr_t)det % es)) return POLSAR_E_ALIGN;
-  if (counters && ((uintptr_t)counters % 8)) return POLSAR_E_ALIGN;
-  if (!z && !inv && !det && !status && !counters) return POLSAR_E_ARG;
-  if (n > 0) {
-    const Range rl = span(s, 6, s_pitch, n, es);
-    const Range rz = z ? span(z, 9, z_pitch, n, es) : Range{0, 0};
-    const Range ri = inv ? span(inv, 9, inv_pitch, n, es) : Range{0, 0};
-    const Range rd = det ? span(det, 1, n, n, es) : Range{0, 0};
-    const Range rs = status ? span(status, 1, n, n, 1) : Range{0, 0};
-    const Range all[5] = {rl, rz, ri, rd, rs};
-    for (int p = 0; p < 5; ++p)
-      for (int q = p + 1; q < 5; ++q)
-        if (all[p].hi > all[p].lo && all[q].hi > all[q].lo && overlap(all[p], all[q])) return POLSAR_E_ALIAS;
-  }
-  if (n == 0) return POLSAR_OK;
-  BoxArgs a{s, s_pitch, z, z_pitch, inv, inv_pitch, det, status, counters, height, width, 0};
-  if (launch_boxcar(dtype, op_code(method, precision), a, radius, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
 }
@@ -1305,7 +976,7 @@ int polsar_blockdiag_inv_det(int dtype, int method, int precision, int64_t n, in
       }
   }
   if (n == 0) return POLSAR_OK;
-  BlockArgs a{n_blocks, block_det, block_det_pitch, InvDetArgs{z, z_pitch, inv, inv_pitch, det, status, counters, n, 0, 0}};
+  BlockArgs a{n_blocks, block_det, block_det_pitch, InvDetArgs{z, z_pitch, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
   const bool vec = vec_ok(z, z_pitch, es) && vec_ok(inv, inv_pitch, es) && vec_ok(det, 0, es) &&
                    vec_ok(block_det, block_det_pitch, es) && (status == nullptr || ((uintptr_t)status % (16 / es)) == 0);
   const polsar_launch c = get_cfg(0, dtype, method, precision);
@@ -1600,7 +1271,7 @@ int polsar_streamer_run(polsar_streamer* s, int64_t n, const void* z, int64_t z_
     if (inv && overlap(span(inv, 9, inv_pitch, n, es), rz)) return POLSAR_E_ALIAS;
     if (det && overlap(span(det, 1, n, n, es), rz)) return POLSAR_E_ALIAS;
   }
-  const polsar_launch c = get_cfg(polsar_inv_det_launch_op(s->chunk), s->dtype, s->method, s->precision);
+  const polsar_launch c = inv_det_cfg(s->chunk, s->dtype, s->method, s->precision, status || counters);
   const int op = op_code(s->method, s->precision);
   const size_t P = (size_t)s->pitch * es;
   hipError_t e = hipSuccess;
@@ -1612,7 +1283,7 @@ int polsar_streamer_run(polsar_streamer* s, int64_t n, const void* z, int64_t z_
     e = hipMemcpy2DAsync(s->dz[b], P, (const char*)z + off * es, (size_t)z_pitch * es, w, 9, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) break;
     InvDetArgs a{s->dz[b], s->pitch, inv ? s->dout[b] : nullptr, s->pitch,
-                 det ? (char*)s->dout[b] + 9 * P : nullptr, status ? s->dst[b] : nullptr, counters, m, 0, 0};
+                 det ? (char*)s->dout[b] + 9 * P : nullptr, status ? s->dst[b] : nullptr, counters, m, 0, 0, 0};
     e = launch_inv_det(s->dtype, op, c, true, a, st);
     if (e != hipSuccess) break;
     if (inv) e = hipMemcpy2DAsync((char*)inv + off * es, (size_t)inv_pitch * es, s->dout[b], P, w, 9, hipMemcpyDeviceToHost, st);
