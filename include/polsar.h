@@ -13,11 +13,10 @@
  * for A = [[a, b, c], [conj(b), d, e], [conj(c), conj(e), f]] (the upper
  * triangle, Section 2.1).  Inverses and gradients use the same packing.
  * Element type is float (POLSAR_F32) or double (POLSAR_F64) for every plane
- * of one call.  pitch >= n.  Pointers must be aligned to the element size;
- * when every plane base is 16-byte aligned (base and pitch*element size
- * multiples of 16, and the status plane 4-byte aligned for F32, 2-byte for
- * F64) the kernels move 64 or 128 bits per access (the launch table's
- * vector_bytes), otherwise one element.
+ * of one call.  pitch >= n.  Pointers must be aligned to the element size
+ * (the status plane to a byte); no more is asked: the kernels move 64 or 128
+ * bits per access (the launch table's vector_bytes) at any such base and
+ * pitch.  Planes on 128-byte lines (polsar_recommended_pitch) stream best.
  *
  * MEMORY AND STREAMS.  Unless stated, pointers are DEVICE pointers on the
  * current HIP device; the caller allocates and owns every buffer, the library
@@ -309,10 +308,11 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *   grid_per_cu  0 = one tile per block; k > 0 = persistent grid of k blocks
  *                per compute unit striding over tiles
  *   nontemporal  1 = streaming (non-temporal) loads and stores
- *   vector_bytes 16 or 8: bytes per lane per plane access on aligned planes
+ *   vector_bytes 16 or 8: bytes per lane per plane access
  *   blocks_per_cu 0 = as many resident blocks as registers allow; k > 0 = at
  *                most k blocks resident per compute unit (enforced by padding
- *                the block's LDS).  On MI355X these streaming kernels move
+ *                the block's LDS; twice that for FP32 compensated calls of
+ *                op 6 that want statuses or counters).  On MI355X these streaming kernels move
  *                more bytes per second with few waves in flight per CU. */
 typedef struct { int block, unroll, grid_per_cu, nontemporal, vector_bytes, blocks_per_cu; } polsar_launch;
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out);

@@ -1,7 +1,7 @@
 // Batched launch over many images of uneven sizes.
 //
 // The images' pixels are cut into tiles of `block` vectors (one vector per
-// lane, V pixels per vector on the 128-bit path), numbered consecutively
+// lane, V pixels per vector), numbered consecutively
 // image after image.  The grid has one block per tile, so the hardware
 // dispatcher hands tiles to compute units as they free up, or is a
 // persistent grid (k blocks per compute unit) that strides over the global
@@ -48,9 +48,7 @@ struct ImgDesc {
   double n_looks;
   int64_t tile0;   // first global tile of this image
   int64_t ntiles;  // tiles of this image
-  int64_t nvec;    // full vectors on this image's path
-  int vec;         // 1: 128-bit path, 0: one element per access
-  int pad;
+  int64_t nvec;    // full vectors
 };
 
 struct BatchArgs {
@@ -207,8 +205,7 @@ __global__ __launch_bounds__(256) void k_batch(BatchArgs a, const ImgDesc* __res
     while (cur + 1 < a.count && img[cur + 1].tile0 <= t) ++cur;
     const ImgDesc& d = img[cur];
     const int64_t lt = t - d.tile0;
-    const double acc = d.vec ? batch_tile<T, OP, VW, NT>(a, d, lt, gscale, c0, c1, c2)
-                             : batch_tile<T, OP, 1, NT>(a, d, lt, gscale, c0, c1, c2);
+    const double acc = batch_tile<T, OP, VW, NT>(a, d, lt, gscale, c0, c1, c2);
     if (a.do_fwd) {
       const double bs = block_sum(acc);
       if (threadIdx.x == 0) a.partial[t] = bs;
@@ -364,26 +361,19 @@ int polsar_batch_create(const polsar_image* imgs, int count, int dtype, int meth
       return p && pitch >= m.n && aligned(p, es);
     };
     if (!planes_ok(m.z, m.z_pitch)) return POLSAR_E_ARG;
-    bool vec = aligned(m.z, 16) && (m.z_pitch * (int64_t)es) % 16 == 0;
     if (ops & POLSAR_OP_INV_DET) {
       if (!m.inv && !m.det && !m.status) return POLSAR_E_ARG;
       if (m.inv && !planes_ok(m.inv, m.inv_pitch)) return POLSAR_E_ARG;
       if (m.det && !aligned(m.det, es)) return POLSAR_E_ALIGN;
-      if (m.inv) vec = vec && aligned(m.inv, 16) && (m.inv_pitch * (int64_t)es) % 16 == 0;
-      if (m.det) vec = vec && aligned(m.det, 16);
-      if (m.status) vec = vec && aligned(m.status, VW);
     }
     if (ops & (POLSAR_OP_WISHART_FWD | POLSAR_OP_WISHART_BWD)) {
       if (!planes_ok(m.sigma, m.s_pitch) || !(m.n_looks > 0.0)) return POLSAR_E_ARG;
-      vec = vec && aligned(m.sigma, 16) && (m.s_pitch * (int64_t)es) % 16 == 0;
     }
     if (ops & POLSAR_OP_WISHART_FWD) {
       if (!m.loss || !aligned(m.loss, 8)) return POLSAR_E_ARG;
-      if (m.ell) vec = vec && aligned(m.ell, 16);
     }
     if (ops & POLSAR_OP_WISHART_BWD) {
       if (!planes_ok(m.grad, m.g_pitch)) return POLSAR_E_ARG;
-      vec = vec && aligned(m.grad, 16) && (m.g_pitch * (int64_t)es) % 16 == 0;
     }
     {  // this image's byte ranges, checked against every image's below
       auto add = [&](const void* p, int planes, int64_t pitch, size_t e, bool is_out) {
@@ -421,9 +411,7 @@ int polsar_batch_create(const polsar_image* imgs, int count, int dtype, int meth
     d.sp = m.s_pitch;
     d.gp = m.g_pitch;
     d.n_looks = m.n_looks;
-    d.vec = vec ? 1 : 0;
-    d.pad = 0;
-    d.nvec = m.n / (vec ? VW : 1);  // VW: the batch's vector width (set above)
+    d.nvec = m.n / VW;  // VW: the batch's vector width (set above)
     d.ntiles = std::max<int64_t>(1, (d.nvec + block - 1) / block);
     d.tile0 = tiles;
     tiles += d.ntiles;
@@ -440,8 +428,7 @@ int polsar_batch_create(const polsar_image* imgs, int count, int dtype, int meth
   b->block = block;
   b->nt = use.nontemporal;
   b->half = half ? 1 : 0;
-  // the FP32 compensated inverse queues rejected pixels in LDS: 64*VW
-  // entries per wave (the one-element path uses the front of that)
+  // the FP32 compensated inverse queues pixels in LDS: 64*VW entries per wave
   const bool queued = b->op == ADJ_COMP && dtype == POLSAR_F32 && (ops & POLSAR_OP_INV_DET);
   b->lds = polsar_launch_lds_bytes(use, queued ? comp_queue_bytes(block, VW) : 0);
   b->total_tiles = tiles;

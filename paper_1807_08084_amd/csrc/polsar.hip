@@ -82,7 +82,7 @@ __device__ __forceinline__ void inv_det_vec(const InvDetArgs& a, const T (&in)[9
 }
 
 template <class T, int OP, int V, int U, bool NT>
-__global__ __launch_bounds__(256, OP == ADJ_COMP && U == 1 ? 4 : 1) void k_inv_det(InvDetArgs a) {
+__global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4 : 1) void k_inv_det(InvDetArgs a) {
   const T* __restrict__ z = (const T*)a.z;
   const int B = blockDim.x;
   unsigned c0 = 0, c1 = 0, c2 = 0;
@@ -658,38 +658,35 @@ hipError_t dispatch_inv_det_v(const polsar_launch& c, InvDetArgs& a, hipStream_t
 }
 
 // Access width: 16 bytes per lane per plane (V = 16 / sizeof(T) pixels),
-// 8 bytes when the launch asks for it, one element when the planes are not
-// 16-byte aligned.
+// 8 bytes when the launch asks for it.
 template <class T, int OP>
-hipError_t dispatch_inv_det(const polsar_launch& c, bool vec, InvDetArgs& a, hipStream_t s) {
+hipError_t dispatch_inv_det(const polsar_launch& c, InvDetArgs& a, hipStream_t s) {
   constexpr int VW = 16 / sizeof(T);
-  if (!vec) return dispatch_inv_det_v<T, OP, 1>(c, a, s);
   if (c.vector_bytes == 8) return dispatch_inv_det_v<T, OP, VW / 2>(c, a, s);
   return dispatch_inv_det_v<T, OP, VW>(c, a, s);
 }
 
-hipError_t launch_inv_det(int dtype, int op, const polsar_launch& c, bool vec, InvDetArgs& a, hipStream_t s) {
+hipError_t launch_inv_det(int dtype, int op, const polsar_launch& c, InvDetArgs& a, hipStream_t s) {
   if (dtype == POLSAR_F32) {
     switch (op) {
-      case ADJ_PLAIN: return dispatch_inv_det<float, ADJ_PLAIN>(c, vec, a, s);
-      case ADJ_COMP: return dispatch_inv_det<float, ADJ_COMP>(c, vec, a, s);
-      case ADJ_WIDE: return dispatch_inv_det<float, ADJ_WIDE>(c, vec, a, s);
-      case CHOL_PLAIN: return dispatch_inv_det<float, CHOL_PLAIN>(c, vec, a, s);
-      case CHOL_COMP: return dispatch_inv_det<float, CHOL_COMP>(c, vec, a, s);
-      default: return dispatch_inv_det<float, CHOL_WIDE>(c, vec, a, s);
+      case ADJ_PLAIN: return dispatch_inv_det<float, ADJ_PLAIN>(c, a, s);
+      case ADJ_COMP: return dispatch_inv_det<float, ADJ_COMP>(c, a, s);
+      case ADJ_WIDE: return dispatch_inv_det<float, ADJ_WIDE>(c, a, s);
+      case CHOL_PLAIN: return dispatch_inv_det<float, CHOL_PLAIN>(c, a, s);
+      case CHOL_COMP: return dispatch_inv_det<float, CHOL_COMP>(c, a, s);
+      default: return dispatch_inv_det<float, CHOL_WIDE>(c, a, s);
     }
   }
   switch (op) {
-    case ADJ_PLAIN: return dispatch_inv_det<double, ADJ_PLAIN>(c, vec, a, s);
-    case ADJ_COMP: return dispatch_inv_det<double, ADJ_COMP>(c, vec, a, s);
-    default: return dispatch_inv_det<double, CHOL_PLAIN>(c, vec, a, s);
+    case ADJ_PLAIN: return dispatch_inv_det<double, ADJ_PLAIN>(c, a, s);
+    case ADJ_COMP: return dispatch_inv_det<double, ADJ_COMP>(c, a, s);
+    default: return dispatch_inv_det<double, CHOL_PLAIN>(c, a, s);
   }
 }
 
-// Validates polsar_inv_det arguments; fills `a` and `vec` on success.
+// Validates polsar_inv_det arguments; fills `a` on success.
 int prepare_inv_det(int dtype, int method, int prec, int64_t n, const void* z, int64_t zp, void* inv,
-                    int64_t ip, void* det, uint8_t* status, unsigned long long* counters, InvDetArgs& a,
-                    bool& vec) {
+                    int64_t ip, void* det, uint8_t* status, unsigned long long* counters, InvDetArgs& a) {
   int r0 = check_mode(dtype, method, prec);
   if (r0) return r0;
   if (n < 0) return POLSAR_E_ARG;
@@ -717,9 +714,6 @@ int prepare_inv_det(int dtype, int method, int prec, int64_t n, const void* z, i
     }
   }
   a = InvDetArgs{z, zp, inv, ip, det, status, counters, n, 0, 0, 0};
-  const int VW = (int)(16 / es);
-  vec = vec_ok(z, zp, es) && vec_ok(inv, ip, es) && vec_ok(det, 0, es) &&
-        (status == nullptr || ((uintptr_t)status % VW) == 0);
   return POLSAR_OK;
 }
 
@@ -740,28 +734,27 @@ hipError_t dispatch_multilook_v(const polsar_launch& c, MultilookArgs& a, hipStr
 }
 
 template <class T, int OP>
-hipError_t dispatch_multilook(const polsar_launch& c, bool vec, MultilookArgs& a, hipStream_t s) {
+hipError_t dispatch_multilook(const polsar_launch& c, MultilookArgs& a, hipStream_t s) {
   constexpr int VW = 16 / sizeof(T);
-  if (!vec) return dispatch_multilook_v<T, OP, 1>(c, a, s);
   if (c.vector_bytes == 8) return dispatch_multilook_v<T, OP, VW / 2>(c, a, s);
   return dispatch_multilook_v<T, OP, VW>(c, a, s);
 }
 
-hipError_t launch_multilook(int dtype, int op, const polsar_launch& c, bool vec, MultilookArgs& a, hipStream_t s) {
+hipError_t launch_multilook(int dtype, int op, const polsar_launch& c, MultilookArgs& a, hipStream_t s) {
   if (dtype == POLSAR_F32) {
     switch (op) {
-      case ADJ_PLAIN: return dispatch_multilook<float, ADJ_PLAIN>(c, vec, a, s);
-      case ADJ_COMP: return dispatch_multilook<float, ADJ_COMP>(c, vec, a, s);
-      case ADJ_WIDE: return dispatch_multilook<float, ADJ_WIDE>(c, vec, a, s);
-      case CHOL_PLAIN: return dispatch_multilook<float, CHOL_PLAIN>(c, vec, a, s);
-      case CHOL_COMP: return dispatch_multilook<float, CHOL_COMP>(c, vec, a, s);
-      default: return dispatch_multilook<float, CHOL_WIDE>(c, vec, a, s);
+      case ADJ_PLAIN: return dispatch_multilook<float, ADJ_PLAIN>(c, a, s);
+      case ADJ_COMP: return dispatch_multilook<float, ADJ_COMP>(c, a, s);
+      case ADJ_WIDE: return dispatch_multilook<float, ADJ_WIDE>(c, a, s);
+      case CHOL_PLAIN: return dispatch_multilook<float, CHOL_PLAIN>(c, a, s);
+      case CHOL_COMP: return dispatch_multilook<float, CHOL_COMP>(c, a, s);
+      default: return dispatch_multilook<float, CHOL_WIDE>(c, a, s);
     }
   }
   switch (op) {
-    case ADJ_PLAIN: return dispatch_multilook<double, ADJ_PLAIN>(c, vec, a, s);
-    case ADJ_COMP: return dispatch_multilook<double, ADJ_COMP>(c, vec, a, s);
-    default: return dispatch_multilook<double, CHOL_PLAIN>(c, vec, a, s);
+    case ADJ_PLAIN: return dispatch_multilook<double, ADJ_PLAIN>(c, a, s);
+    case ADJ_COMP: return dispatch_multilook<double, ADJ_COMP>(c, a, s);
+    default: return dispatch_multilook<double, CHOL_PLAIN>(c, a, s);
   }
 }
 
@@ -781,26 +774,26 @@ hipError_t dispatch_block_v(const polsar_launch& c, BlockArgs& a, hipStream_t s)
 }
 
 template <class T, int OP>
-hipError_t dispatch_block(const polsar_launch& c, bool vec, BlockArgs& a, hipStream_t s) {
+hipError_t dispatch_block(const polsar_launch& c, BlockArgs& a, hipStream_t s) {
   constexpr int VW = 16 / sizeof(T);
-  return vec ? dispatch_block_v<T, OP, VW>(c, a, s) : dispatch_block_v<T, OP, 1>(c, a, s);
+  return dispatch_block_v<T, OP, VW>(c, a, s);
 }
 
-hipError_t launch_block(int dtype, int op, const polsar_launch& c, bool vec, BlockArgs& a, hipStream_t s) {
+hipError_t launch_block(int dtype, int op, const polsar_launch& c, BlockArgs& a, hipStream_t s) {
   if (dtype == POLSAR_F32) {
     switch (op) {
-      case ADJ_PLAIN: return dispatch_block<float, ADJ_PLAIN>(c, vec, a, s);
-      case ADJ_COMP: return dispatch_block<float, ADJ_COMP>(c, vec, a, s);
-      case ADJ_WIDE: return dispatch_block<float, ADJ_WIDE>(c, vec, a, s);
-      case CHOL_PLAIN: return dispatch_block<float, CHOL_PLAIN>(c, vec, a, s);
-      case CHOL_COMP: return dispatch_block<float, CHOL_COMP>(c, vec, a, s);
-      default: return dispatch_block<float, CHOL_WIDE>(c, vec, a, s);
+      case ADJ_PLAIN: return dispatch_block<float, ADJ_PLAIN>(c, a, s);
+      case ADJ_COMP: return dispatch_block<float, ADJ_COMP>(c, a, s);
+      case ADJ_WIDE: return dispatch_block<float, ADJ_WIDE>(c, a, s);
+      case CHOL_PLAIN: return dispatch_block<float, CHOL_PLAIN>(c, a, s);
+      case CHOL_COMP: return dispatch_block<float, CHOL_COMP>(c, a, s);
+      default: return dispatch_block<float, CHOL_WIDE>(c, a, s);
     }
   }
   switch (op) {
-    case ADJ_PLAIN: return dispatch_block<double, ADJ_PLAIN>(c, vec, a, s);
-    case ADJ_COMP: return dispatch_block<double, ADJ_COMP>(c, vec, a, s);
-    default: return dispatch_block<double, CHOL_PLAIN>(c, vec, a, s);
+    case ADJ_PLAIN: return dispatch_block<double, ADJ_PLAIN>(c, a, s);
+    case ADJ_COMP: return dispatch_block<double, ADJ_COMP>(c, a, s);
+    default: return dispatch_block<double, CHOL_PLAIN>(c, a, s);
   }
 }
 
@@ -816,9 +809,9 @@ hipError_t go_wishart(const polsar_launch& c, int64_t grid, WishartArgs& a, hipS
 }
 
 // Pixels per access of a Wishart launch, and its tiles (one partial sum each).
-int wishart_vector(const polsar_launch& c, bool vec, size_t es) {
+int wishart_vector(const polsar_launch& c, size_t es) {
   const int vw = (int)(16 / es);
-  return !vec ? 1 : (c.vector_bytes == 8 ? vw / 2 : vw);
+  return c.vector_bytes == 8 ? vw / 2 : vw;
 }
 int64_t wishart_tiles(const polsar_launch& c, int v, int64_t n) {
   const int64_t per_tile = (int64_t)c.block * c.unroll;
@@ -834,9 +827,8 @@ hipError_t dispatch_wishart_v(const polsar_launch& c, WishartArgs& a, hipStream_
 }
 
 template <class T>
-hipError_t dispatch_wishart(const polsar_launch& c, bool vec, WishartArgs& a, hipStream_t s) {
+hipError_t dispatch_wishart(const polsar_launch& c, WishartArgs& a, hipStream_t s) {
   constexpr int VW = 16 / sizeof(T);
-  if (!vec) return dispatch_wishart_v<T, 1>(c, a, s);
   if (c.vector_bytes == 8) return dispatch_wishart_v<T, VW / 2>(c, a, s);
   return dispatch_wishart_v<T, VW>(c, a, s);
 }
@@ -903,12 +895,11 @@ int polsar_set_launch(int op, int dtype, int method, int precision, const polsar
 int polsar_inv_det(int dtype, int method, int precision, int64_t n, const void* z, int64_t z_pitch, void* inv,
                    int64_t inv_pitch, void* det, uint8_t* status, unsigned long long* counters, void* stream) {
   InvDetArgs a;
-  bool vec = false;
-  int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, status, counters, a, vec);
+  int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, status, counters, a);
   if (r) return r;
   if (n == 0) return POLSAR_OK;
   const polsar_launch c = inv_det_cfg(n, dtype, method, precision, status || counters);
-  if (launch_inv_det(dtype, op_code(method, precision), c, vec, a, (hipStream_t)stream) != hipSuccess)
+  if (launch_inv_det(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
 }
@@ -940,10 +931,8 @@ int polsar_multilook_inv_det(int dtype, int method, int precision, int64_t n, in
   if (n == 0) return POLSAR_OK;
   MultilookArgs a{looks, looks_pitch, n_looks, 1.0 / n_looks, z, z_pitch,
                   InvDetArgs{nullptr, 0, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
-  const bool vec = vec_ok(looks, looks_pitch, es) && vec_ok(z, z_pitch, es) && vec_ok(inv, inv_pitch, es) && vec_ok(det, 0, es) &&
-        (status == nullptr || ((uintptr_t)status % (16 / es)) == 0);
   const polsar_launch c = get_cfg(2, dtype, method, precision);
-  if (launch_multilook(dtype, op_code(method, precision), c, vec, a, (hipStream_t)stream) != hipSuccess)
+  if (launch_multilook(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
 }
@@ -977,10 +966,8 @@ int polsar_blockdiag_inv_det(int dtype, int method, int precision, int64_t n, in
   }
   if (n == 0) return POLSAR_OK;
   BlockArgs a{n_blocks, block_det, block_det_pitch, InvDetArgs{z, z_pitch, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
-  const bool vec = vec_ok(z, z_pitch, es) && vec_ok(inv, inv_pitch, es) && vec_ok(det, 0, es) &&
-                   vec_ok(block_det, block_det_pitch, es) && (status == nullptr || ((uintptr_t)status % (16 / es)) == 0);
   const polsar_launch c = get_cfg(0, dtype, method, precision);
-  if (launch_block(dtype, op_code(method, precision), c, vec, a, (hipStream_t)stream) != hipSuccess) return POLSAR_E_HIP;
+  if (launch_block(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess) return POLSAR_E_HIP;
   return POLSAR_OK;
 }
 
@@ -1033,11 +1020,9 @@ int polsar_wishart_call(int dtype, int pass, int64_t n, const void* sigma, int64
         return POLSAR_E_ALIAS;
     }
   }
-  const bool vec = n > 0 && vec_ok(sigma, s_pitch, es) && vec_ok(z, z_pitch, es) &&
-                   (!bwd || vec_ok(grad, g_pitch, es)) && (!(fwd && ell) || vec_ok(ell, 0, es));
   const polsar_launch c = get_cfg(polsar_wishart_launch_op(n), dtype, 0, 0);
   if (fwd && n > 0 && !ws_user) {
-    if (wishart_tiles(c, wishart_vector(c, vec, es), n) > ws_words) return POLSAR_E_WORKSPACE;
+    if (wishart_tiles(c, wishart_vector(c, es), n) > ws_words) return POLSAR_E_WORKSPACE;
     if ((r = fixed_ws(&ws))) return r;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -1051,7 +1036,7 @@ int polsar_wishart_call(int dtype, int pass, int64_t n, const void* sigma, int64
   }
   WishartArgs a{sigma, s_pitch, z, z_pitch, n_looks, fwd ? ell : nullptr, fwd ? ws : nullptr, grad_loss,
                 bwd ? grad : nullptr, g_pitch, counters, n, 0, 0, fwd ? 1 : 0, bwd ? 1 : 0};
-  hipError_t e = dtype == POLSAR_F32 ? dispatch_wishart<float>(c, vec, a, s) : dispatch_wishart<double>(c, vec, a, s);
+  hipError_t e = dtype == POLSAR_F32 ? dispatch_wishart<float>(c, a, s) : dispatch_wishart<double>(c, a, s);
   if (e != hipSuccess) return POLSAR_E_HIP;
   if (fwd) {
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(REDUCE_BLOCK), 0, s, (const double*)ws, a.tiles, loss);
@@ -1074,8 +1059,7 @@ int polsar_autotune_inv_det(int dtype, int method, int precision, int64_t n, con
                             void* inv, int64_t inv_pitch, void* det, int reps, polsar_launch* best,
                             float* best_ms, void* stream) {
   InvDetArgs a;
-  bool vec = false;
-  int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, nullptr, nullptr, a, vec);
+  int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, nullptr, nullptr, a);
   if (r) return r;
   if (n == 0 || reps <= 0) return POLSAR_E_ARG;
   hipStream_t s = (hipStream_t)stream;
@@ -1093,11 +1077,11 @@ int polsar_autotune_inv_det(int dtype, int method, int precision, int64_t n, con
   // untimed call; negative on a HIP error
   auto time_cfg = [&](const polsar_launch& c) -> float {
     InvDetArgs aa = a;
-    if (launch_inv_det(dtype, op, c, vec, aa, s) != hipSuccess) return -1.f;
+    if (launch_inv_det(dtype, op, c, aa, s) != hipSuccess) return -1.f;
     (void)hipEventRecord(e0, s);
     for (int i = 0; i < reps; ++i) {
       aa = a;
-      (void)launch_inv_det(dtype, op, c, vec, aa, s);
+      (void)launch_inv_det(dtype, op, c, aa, s);
     }
     (void)hipEventRecord(e1, s);
     if (hipEventSynchronize(e1) != hipSuccess) return -1.f;
@@ -1284,7 +1268,7 @@ int polsar_streamer_run(polsar_streamer* s, int64_t n, const void* z, int64_t z_
     if (e != hipSuccess) break;
     InvDetArgs a{s->dz[b], s->pitch, inv ? s->dout[b] : nullptr, s->pitch,
                  det ? (char*)s->dout[b] + 9 * P : nullptr, status ? s->dst[b] : nullptr, counters, m, 0, 0, 0};
-    e = launch_inv_det(s->dtype, op, c, true, a, st);
+    e = launch_inv_det(s->dtype, op, c, a, st);
     if (e != hipSuccess) break;
     if (inv) e = hipMemcpy2DAsync((char*)inv + off * es, (size_t)inv_pitch * es, s->dout[b], P, w, 9, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && det) e = hipMemcpyAsync((char*)det + off * es, (char*)s->dout[b] + 9 * P, w, hipMemcpyDeviceToHost, st);
