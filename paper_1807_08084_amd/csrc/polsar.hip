@@ -509,9 +509,11 @@ polsar_launch default_launch(int op, int dtype, int method, int prec) {
              // image: 357 us, 370 with 8 blocks of 256 lanes)
       if (!f64 && !chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 8, 6};
       return f64 ? polsar_launch{256, 1, 0, 1, 8, 4} : polsar_launch{128, 1, 0, 1, 16, 0};
-    case 3:  // FP32: one block of 128 lanes per tile, 8-byte accesses (64-image batch: 0.72 of HBM, against
-             // 0.67 for the best persistent grid, 2 blocks of 256 lanes per CU)
-      return f64 ? polsar_launch{256, 1, 2, 1, 16, 6} : polsar_launch{128, 1, 0, 1, 8, 0};
+    case 3:  // one block of 128 lanes per tile, 8-byte accesses.  FP32, 12 images of 128..2048 and of 1024..2048
+             // a side: 219 and 614 us at 6 blocks per CU, 221 and 624 without a cap.  FP64, 12 images of 128..1024
+             // and of 1024 a side: 156 and 697 us at 5, 154 and 748 at 6; a persistent grid of 2 blocks of 256
+             // lanes, 169 and 844
+      return f64 ? polsar_launch{128, 1, 0, 1, 8, 5} : polsar_launch{128, 1, 0, 1, 8, 6};
     case 4:  // copy probe: few waves in flight stream best
       return polsar_launch{64, 1, 0, 1, 16, 5};
     case 6:  // the inverse kernel on images of at least INV_DET_LARGE pixels
