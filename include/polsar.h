@@ -312,7 +312,8 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *   blocks_per_cu 0 = as many resident blocks as registers allow; k > 0 = at
  *                most k blocks resident per compute unit (enforced by padding
  *                the block's LDS; twice that for FP32 compensated calls of
- *                op 6 that want statuses or counters).  On MI355X these streaming kernels move
+ *                op 6 that want statuses or counters and for Wishart calls
+ *                that write no gradient).  On MI355X these streaming kernels move
  *                more bytes per second with few waves in flight per CU. */
 typedef struct { int block, unroll, grid_per_cu, nontemporal, vector_bytes, blocks_per_cu; } polsar_launch;
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out);

@@ -581,6 +581,19 @@ polsar_launch inv_det_cfg(int64_t n, int dtype, int method, int prec, bool want_
   return c;
 }
 
+// The Wishart kernel's launch.  A pass that writes no gradient runs twice the
+// resident blocks of the table: the cap is there for the nine write streams,
+// and a pass without them is bound by its reads in flight (forward alone,
+// FP32 2048x2048: 57 us, 65 with the table's 5; FP64 4096x4096: 359 with 8,
+// 428 with 4).  The
+// tiles stay those of the table, so the partial sums and the loss have the
+// same bits as the fused pass's.
+polsar_launch wishart_cfg(int64_t n, int dtype, bool bwd) {
+  polsar_launch c = get_cfg(polsar_wishart_launch_op(n), dtype, 0, 0);
+  if (!bwd) c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
+  return c;
+}
+
 bool valid_launch(const polsar_launch& c, int op) {
   if (c.block != 64 && c.block != 128 && c.block != 256) return false;
   if (c.unroll != 1 && c.unroll != 2 && !((op == 0 || op == 6) && c.unroll == 4)) return false;
@@ -1022,7 +1035,7 @@ int polsar_wishart_call(int dtype, int pass, int64_t n, const void* sigma, int64
         return POLSAR_E_ALIAS;
     }
   }
-  const polsar_launch c = get_cfg(polsar_wishart_launch_op(n), dtype, 0, 0);
+  const polsar_launch c = wishart_cfg(n, dtype, bwd);
   if (fwd && n > 0 && !ws_user) {
     if (wishart_tiles(c, wishart_vector(c, es), n) > ws_words) return POLSAR_E_WORKSPACE;
     if ((r = fixed_ws(&ws))) return r;
