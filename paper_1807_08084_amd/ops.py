@@ -9,6 +9,7 @@ Work is enqueued on torch's current stream.
 from __future__ import annotations
 
 import ctypes
+import math
 
 import torch
 
@@ -26,38 +27,62 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"planes must be float32 or float64, got {t.dtype}")
 
 
+def _layout(t: torch.Tensor) -> tuple[int, int, bool]:
+    """(elements, pitch, contiguous) of the planes of t (k, ...): what
+    t[0].numel(), t.stride(0) and t[0].is_contiguous() say, without a view."""
+    shape, strides = t.shape, t.stride()
+    n, dense = 1, True
+    for d in range(len(shape) - 1, 0, -1):
+        if shape[d] != 1 and strides[d] != n:
+            dense = False
+        n *= shape[d]
+    return n, strides[0], dense or n == 0
+
+
 def _planes(t: torch.Tensor, name: str) -> tuple[int, int]:
     """(n, pitch) of a (9, ...) plane tensor; each plane must be contiguous."""
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dim() < 2 or t.shape[0] != 9:
         raise ValueError(f"{name} must have shape (9, ...), got {tuple(t.shape)}")
-    n = t[0].numel()
-    if not t[0].is_contiguous():
+    n, pitch, dense = _layout(t)
+    if not dense:
         raise ValueError(f"{name}: each plane must be contiguous")
-    return n, t.stride(0)
+    return n, pitch
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The raw stream: the given one, or torch's current one on the current device."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def recommended_pitch(dtype: torch.dtype, n: int) -> int:
     return int(L.lib().polsar_recommended_pitch(L.F32 if dtype == torch.float32 else L.F64, int(n)))
 
 
+def _planes_and_one(k: int, shape, dtype: torch.dtype, device) -> tuple[torch.Tensor, torch.Tensor]:
+    """Uninitialised (k, *shape) planes and one more plane (*shape) in a
+    buffer of k + 1 planes with the recommended pitch."""
+    n, strides = 1, [0] * len(shape)
+    for d in range(len(shape) - 1, -1, -1):
+        strides[d] = n
+        n *= shape[d] or 1
+    pitch = recommended_pitch(dtype, n if 0 not in shape else 0)
+    buf = torch.empty((k + 1, pitch), dtype=dtype, device=device)
+    return buf.as_strided((k, *shape), (pitch, *strides)), buf.as_strided(shape, strides, k * pitch)
+
+
 def empty_planes(k: int, shape, dtype: torch.dtype, device="cuda") -> torch.Tensor:
     """Uninitialised (k, *shape) planes laid out with the recommended pitch
     (a view into a (k, pitch) buffer; each plane contiguous)."""
     shape = tuple(shape) if isinstance(shape, (tuple, list, torch.Size)) else (int(shape),)
-    n = 1
-    for s in shape:
-        n *= s
+    n = math.prod(shape)
     buf = torch.empty((k, recommended_pitch(dtype, n)), dtype=dtype, device=device)
     return buf[:, :n].view((k,) + shape) if len(shape) > 1 else buf[:, :n]
 
@@ -84,11 +109,12 @@ def inv_det(z: torch.Tensor, method: str = "adjugate", precision: str = "compens
     n, zp = _planes(z, "z")
     shape = z.shape[1:]
     if inv is None and det is None and want_inv and want_det:
-        out = empty_planes(10, shape, z.dtype, z.device)  # 9 inverse planes + det, one pitch
-        inv, det = out[:9], out[9]
-    if inv is None and want_inv:
-        inv = empty_planes(9, shape, z.dtype, z.device)
-    ip = _planes(inv, "inv")[1] if inv is not None else 0
+        inv, det = _planes_and_one(9, shape, z.dtype, z.device)
+        ip = inv.stride(0)
+    else:
+        if inv is None and want_inv:
+            inv = empty_planes(9, shape, z.dtype, z.device)
+        ip = _planes(inv, "inv")[1] if inv is not None else 0
     if det is None and want_det:
         det = torch.empty(shape, dtype=z.dtype, device=z.device)
     st = None
@@ -113,12 +139,11 @@ def multilook_inv_det(looks: torch.Tensor, n_looks: int, method: str = "adjugate
     dt = _dtype_code(looks)
     if looks.dim() < 2 or looks.shape[0] != 6 * n_looks:
         raise ValueError(f"looks must have shape (6N, ...) with N={n_looks}")
-    if not looks.is_cuda or not looks[0].is_contiguous():
+    n, lp, dense = _layout(looks)
+    if not looks.is_cuda or not dense:
         raise ValueError("looks must be GPU planes, each contiguous")
     shape = looks.shape[1:]
-    n, lp = looks[0].numel(), looks.stride(0)
-    out = empty_planes(10, shape, looks.dtype, looks.device)
-    inv, det = out[:9], out[9]
+    inv, det = _planes_and_one(9, shape, looks.dtype, looks.device)
     z = empty_planes(9, shape, looks.dtype, looks.device) if want_z else None
     st = torch.empty(shape, dtype=torch.uint8, device=looks.device) if status else None
     rc = L.lib().polsar_multilook_inv_det(dt, _METHODS[method], _PRECS[precision], n, int(n_looks), _ptr(looks),
@@ -135,12 +160,11 @@ def boxcar_inv_det(s: torch.Tensor, radius: int, method: str = "adjugate", preci
 
     Returns (z or None, inv, det, status or None), shaped (9, H, W) / (H, W)."""
     dt = _dtype_code(s)
-    if s.dim() != 3 or s.shape[0] != 6 or not s.is_cuda or not s[0].is_contiguous():
+    if s.dim() != 3 or s.shape[0] != 6 or not s.is_cuda or not _layout(s)[2]:
         raise ValueError("s must be GPU planes of shape (6, H, W), each contiguous")
     H, W = int(s.shape[1]), int(s.shape[2])
     shape = (H, W)
-    out = empty_planes(10, shape, s.dtype, s.device)
-    inv, det = out[:9], out[9]
+    inv, det = _planes_and_one(9, shape, s.dtype, s.device)
     z = empty_planes(9, shape, s.dtype, s.device) if want_z else None
     st = torch.empty(shape, dtype=torch.uint8, device=s.device) if status else None
     rc = L.lib().polsar_boxcar_inv_det(dt, _METHODS[method], _PRECS[precision], H, W, int(radius), _ptr(s),
@@ -155,12 +179,11 @@ def blockdiag_inv_det(z: torch.Tensor, n_blocks: int, method: str = "adjugate", 
                       stream=None):
     """Block-diagonal pixels: z (9K, ...) -> (inv (9K, ...), det product, block dets or None, status or None)."""
     dt = _dtype_code(z)
-    if z.dim() < 2 or z.shape[0] != 9 * n_blocks or not z.is_cuda or not z[0].is_contiguous():
+    if z.dim() < 2 or z.shape[0] != 9 * n_blocks or not z.is_cuda or not _layout(z)[2]:
         raise ValueError(f"z must be GPU planes of shape (9*{n_blocks}, ...)")
     shape = z.shape[1:]
-    n, zp = z[0].numel(), z.stride(0)
-    out = empty_planes(9 * n_blocks + 1, shape, z.dtype, z.device)
-    inv, det = out[:9 * n_blocks], out[9 * n_blocks]
+    n, zp, _ = _layout(z)
+    inv, det = _planes_and_one(9 * n_blocks, shape, z.dtype, z.device)
     bd = empty_planes(n_blocks, shape, z.dtype, z.device) if block_det else None
     st = torch.empty(shape, dtype=torch.uint8, device=z.device) if status else None
     rc = L.lib().polsar_blockdiag_inv_det(dt, _METHODS[method], _PRECS[precision], n, int(n_blocks), _ptr(z), zp,
@@ -222,11 +245,11 @@ def nlm_wishart(z: torch.Tensor, aux: torch.Tensor, n_looks: float, radius: int,
     planes for "kl", the (H, W) determinant plane for "bhattacharyya" (as
     inv_det returns them).  Returns (out (9, H, W), wsum (H, W) or None)."""
     dt = _dtype_code(z)
-    if z.dim() != 3 or z.shape[0] != 9 or not z.is_cuda or not z[0].is_contiguous():
+    if z.dim() != 3 or z.shape[0] != 9 or not z.is_cuda or not _layout(z)[2]:
         raise ValueError("z must be GPU planes of shape (9, H, W), each plane contiguous")
     H, W = z.shape[1], z.shape[2]
     if distance == "kl":
-        if aux.shape != z.shape or not aux[0].is_contiguous():
+        if aux.shape != z.shape or not _layout(aux)[2]:
             raise ValueError("aux must be the (9, H, W) inverse planes")
         ap = aux.stride(0)
     else:
@@ -271,15 +294,17 @@ def wishart_loglik(sigma: torch.Tensor, z: torch.Tensor, n_looks: float, *, forw
         grad = None
     elif grad is None:
         grad = empty_planes(9, sigma.shape[1:], sigma.dtype, sigma.device)
-    elif grad.dtype != sigma.dtype or grad[0].numel() != n:
+    elif grad.dtype != sigma.dtype or _layout(grad)[0] != n:
         raise ValueError("grad must match sigma")
     gp = _planes(grad, "grad")[1] if grad is not None else 0
     el = torch.empty(sigma.shape[1:], dtype=sigma.dtype, device=sigma.device) if (ell and forward) else None
-    wsb = workspace_bytes(sigma.dtype, n) if forward else 0
-    if forward and (workspace is None or workspace.numel() * workspace.element_size() < wsb):
-        workspace = torch.empty(max(1, (wsb + 7) // 8), dtype=torch.float64, device=sigma.device)
+    if forward:
+        wsb = workspace_bytes(sigma.dtype, n)
+        if workspace is None or workspace.numel() * workspace.element_size() < wsb:
+            workspace = torch.empty(max(1, (wsb + 7) // 8), dtype=torch.float64, device=sigma.device)
     if grad_loss is not None:
-        grad_loss = grad_loss.to(dtype=torch.float64).reshape(()).contiguous()
+        if grad_loss.dtype != torch.float64 or grad_loss.dim():
+            grad_loss = grad_loss.to(dtype=torch.float64).reshape(())
     ws_size = workspace.numel() * workspace.element_size() if workspace is not None else 0
     rc = L.lib().polsar_wishart_loglik(dt, mode, n, _ptr(sigma), sp, _ptr(z), zp, float(n_looks),
                                        _ptr(loss), _ptr(el), _ptr(grad_loss), _ptr(grad), gp,
@@ -307,7 +332,10 @@ class WishartNLL(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g):
         sigma, z = ctx.saved_tensors
-        _, grad, _ = wishart_loglik(sigma, z, ctx.n_looks, forward=False, backward=True, grad_loss=g)
+        # contiguous: autograd takes such a gradient over as a leaf's .grad; padded planes it would clone
+        # (FP32 2048x2048: 52 us, more than half of the backward kernel's time)
+        grad = torch.empty(sigma.shape, dtype=sigma.dtype, device=sigma.device)
+        wishart_loglik(sigma, z, ctx.n_looks, forward=False, backward=True, grad_loss=g, grad=grad)
         return grad, None, None
 
 
