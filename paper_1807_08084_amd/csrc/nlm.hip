@@ -171,8 +171,8 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
         if (k * E + e < F) q[k * E + e < F ? k * E + e : 0] = v[e];
     }
   };
-  auto pair = [&](int g, const T (&q)[F]) {
-    T w;
+  // the distance's sum over the pair's components
+  auto score = [&](int g, const T (&q)[F]) -> T {
     if constexpr (DIST == 0) {
       T tt = P[g][9] * q[0];
       tt = fma(q[9], P[g][0], tt);
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
         tt = fma(P[g][9 + k], q[k], tt);
         tt = fma(q[9 + k], P[g][k], tt);
       }
-      w = exp2_(alpha * tt + beta);
+      return tt;
     } else if constexpr (MIX) {
       T tt = detp[g] + q[18];
 #pragma unroll
@@ -189,17 +189,51 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
         tt = fma(P[g][9 + k], q[k], tt);
         tt = fma(q[9 + k], P[g][k], tt);
       }
-      w = exp2_(fma(alpha, log2_(tt), lp[g] + q[19]));
+      return tt;
     } else {
       T mm[9], cf[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) mm[k] = P[g][k] + q[k];
       px::cofactors_plain(mm, cf);
-      w = exp2_(alpha * (log2_(px::det_from_cofactors(mm, cf)) - T(0.5) * (lp[g] + q[9])) + beta);
+      return px::det_from_cofactors(mm, cf);
     }
+  };
+  // tt: the score, in MIX its logarithm
+  auto accumulate = [&](int g, T tt, const T (&q)[F]) {
+    T w;
+    if constexpr (DIST == 0) w = exp2_(alpha * tt + beta);
+    else if constexpr (MIX) w = exp2_(fma(alpha, tt, lp[g] + q[19]));
+    else w = exp2_(alpha * (log2_(tt) - T(0.5) * (lp[g] + q[9])) + beta);
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[g][k] += w * q[k];
     ws[g] += w;
+  };
+  // A neighbour against the outputs [lo, hi].  log2f is the hardware's
+  // logarithm but for subnormal numbers, which it scales first: 5 operations a
+  // pair that are left to waves that meet one (B, FP32, 2048x2048, r = 7: 951 ->
+  // 920 us; 256x256, r = 11: 52 -> 48).
+  auto neighbour = [&](int lo, int hi, const T (&q)[F]) {
+    T tt[G];
+    bool small = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      tt[g] = score(g, q);
+      if constexpr (MIX) small |= tt[g] < T(1.17549435e-38f);
+    }
+    if constexpr (MIX) {
+      T lg[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) lg[g] = __builtin_amdgcn_logf(tt[g]);
+      if (__builtin_expect(__any(small), 0)) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) lg[g] = log2_(tt[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) tt[g] = lg[g];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (g >= lo && g <= hi) accumulate(g, tt[g], q);
   };
 
   // input row s of the tile is image row y0 - r + s; row g of the outputs has
@@ -245,17 +279,14 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
       for (int d = 0; d <= 2 * r; ++d) {
         T q[F];
         read(lane + d, q);
-#pragma unroll
-        for (int g = 0; g < G; ++g) pair(g, q);
+        neighbour(0, G - 1, q);
       }
     } else {
 #pragma unroll 1
       for (int d = dlo; d <= dhi; ++d) {
         T q[F];
         read(lane + d, q);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (g >= g_lo && g <= g_hi) pair(g, q);
+        neighbour(g_lo, g_hi, q);
       }
     }
   }
