@@ -313,8 +313,10 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *                most k blocks resident per compute unit (enforced by padding
  *                the block's LDS; twice that for FP32 compensated calls of
  *                op 6 that want statuses or counters and for Wishart calls
- *                that write no gradient).  On MI355X these streaming kernels move
- *                more bytes per second with few waves in flight per CU. */
+ *                that write no gradient, one less for FP32 compensated
+ *                multilooks of at least 4 looks that store Z).  On MI355X
+ *                these streaming kernels move more bytes per second with few
+ *                waves in flight per CU. */
 typedef struct { int block, unroll, grid_per_cu, nontemporal, vector_bytes, blocks_per_cu; } polsar_launch;
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out);
 int polsar_set_launch(int op, int dtype, int method, int precision, const polsar_launch* cfg);

@@ -40,7 +40,7 @@ struct InvDetArgs {
   int64_t n;      // pixels
   int64_t nvec;   // full vectors: n / V
   int64_t tiles;  // ceil(nvec / (block * U)), at least 1
-  int64_t tail;   // the block of the last tile: it takes the n mod V pixels after the last full vector
+  int64_t tail;   // the block of the last tile
 };
 
 // Stores of one pixel-vector's results.
@@ -81,11 +81,38 @@ __device__ __forceinline__ void inv_det_vec(const InvDetArgs& a, const T (&in)[9
   store_vec<T, V, NT>(a, out, dt, st, v);
 }
 
+// Where a kernel takes the pixels after the last full vector: inside the loop
+// over tiles the compiler keeps that code's addresses and constants in
+// registers throughout, 162 instead of 127 for the FP32 compensated inverse
+// (V = 4), whose queue needs the waves.  The other forms stream better with
+// few waves resident, and the registers hold their number down: after the
+// loop, us on 4096x4096, FP64 compensated 412 (in it, 405), FP32 plain 203
+// (199), wide 212 (202), compensated Cholesky 216 (204); three FP64 bands of
+// 2000x2001, 344 (315).
+template <class T, int OP>
+constexpr bool TAIL_AFTER = OP == ADJ_COMP && std::is_same<T, float>::value;
+
 template <class T, int OP, int V, int U, bool NT>
 __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4 : 1) void k_inv_det(InvDetArgs a) {
   const T* __restrict__ z = (const T*)a.z;
   const int B = blockDim.x;
   unsigned c0 = 0, c1 = 0, c2 = 0;
+  // the n mod V pixels after the last full vector
+  auto tail = [&]() {
+    const int64_t i = a.nvec * V + threadIdx.x;
+    if (i < a.n) {
+      T zz[9], xx[9], dt;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) zz[k] = z[k * a.zp + i];
+      const int st = run_pixel<T, OP>(zz, xx, dt, a.status || a.counters);
+      tally(st, c0, c1, c2);
+      if (a.inv)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ((T*)a.inv)[k * a.ip + i] = xx[k];
+      if (a.det) ((T*)a.det)[i] = dt;
+      if (a.status) a.status[i] = (uint8_t)st;
+    }
+  };
   for (int64_t tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
     const int64_t v0 = tile * (int64_t)(B * U) + threadIdx.x;
     if constexpr (OP == ADJ_COMP && std::is_same<T, float>::value) {
@@ -127,24 +154,9 @@ __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4
         if (v < a.nvec) inv_det_vec<T, OP, V, NT>(a, in[u], v, c0, c1, c2);
       }
     }
+    if (V > 1 && !TAIL_AFTER<T, OP> && tile == a.tiles - 1) tail();
   }
-  // after the loop: inside it, the compiler keeps its addresses and constants
-  // in registers across the tiles (172 registers instead of 118 at V = 2)
-  if (V > 1 && blockIdx.x == a.tail) {
-    const int64_t i = a.nvec * V + threadIdx.x;
-    if (i < a.n) {
-      T zz[9], xx[9], dt;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) zz[k] = z[k * a.zp + i];
-      const int st = run_pixel<T, OP>(zz, xx, dt, a.status || a.counters);
-      tally(st, c0, c1, c2);
-      if (a.inv)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) ((T*)a.inv)[k * a.ip + i] = xx[k];
-      if (a.det) ((T*)a.det)[i] = dt;
-      if (a.status) a.status[i] = (uint8_t)st;
-    }
-  }
+  if (V > 1 && TAIL_AFTER<T, OP> && blockIdx.x == a.tail) tail();
   if (a.counters) flush_counters(a.counters, c0, c1, c2);
 }
 
@@ -172,6 +184,32 @@ __global__ __launch_bounds__(256) void k_multilook(MultilookArgs a) {
   const int B = blockDim.x;
   unsigned c0 = 0, c1 = 0, c2 = 0;
   const double inv_n = a.inv_n;
+  // the n mod V pixels after the last full vector
+  auto tail = [&]() {
+    const int64_t i = a.o.nvec * V + threadIdx.x;
+    if (i < a.o.n) {
+      double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+      for (int look = 0; look < a.n_looks; ++look) {
+        T s6[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) s6[j] = S[(int64_t)(6 * look + j) * a.lp + i];
+        px::look_accumulate(s6, acc);
+      }
+      T zz[9], xx[9], dt;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) zz[k] = (T)(acc[k] * inv_n);
+      if (a.z)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ((T*)a.z)[k * a.zp + i] = zz[k];
+      const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
+      tally(st, c0, c1, c2);
+      if (a.o.inv)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[k * a.o.ip + i] = xx[k];
+      if (a.o.det) ((T*)a.o.det)[i] = dt;
+      if (a.o.status) a.o.status[i] = (uint8_t)st;
+    }
+  };
   for (int64_t tile = blockIdx.x; tile < a.o.tiles; tile += gridDim.x) {
     const int64_t v = tile * (int64_t)B + threadIdx.x;
     if (v < a.o.nvec) {
@@ -222,32 +260,9 @@ __global__ __launch_bounds__(256) void k_multilook(MultilookArgs a) {
         inv_det_vec<T, OP, V, NT>(a.o, zz, v, c0, c1, c2);
       }
     }
+    if (V > 1 && !TAIL_AFTER<T, OP> && tile == a.o.tiles - 1) tail();
   }
-  if (V > 1 && blockIdx.x == a.o.tail) {
-    const int64_t i = a.o.nvec * V + threadIdx.x;
-    if (i < a.o.n) {
-      double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-      for (int look = 0; look < a.n_looks; ++look) {
-        T s6[6];
-#pragma unroll
-        for (int j = 0; j < 6; ++j) s6[j] = S[(int64_t)(6 * look + j) * a.lp + i];
-        px::look_accumulate(s6, acc);
-      }
-      T zz[9], xx[9], dt;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) zz[k] = (T)(acc[k] * inv_n);
-      if (a.z)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) ((T*)a.z)[k * a.zp + i] = zz[k];
-      const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
-      tally(st, c0, c1, c2);
-      if (a.o.inv)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[k * a.o.ip + i] = xx[k];
-      if (a.o.det) ((T*)a.o.det)[i] = dt;
-      if (a.o.status) a.o.status[i] = (uint8_t)st;
-    }
-  }
+  if (V > 1 && TAIL_AFTER<T, OP> && blockIdx.x == a.o.tail) tail();
   if (a.o.counters) flush_counters(a.o.counters, c0, c1, c2);
 }
 
@@ -299,27 +314,27 @@ __global__ __launch_bounds__(256) void k_blockdiag(BlockArgs a) {
       if (a.o.det) store_v<T, V, NT>((T*)a.o.det + v * V, prod);
       if (a.o.status) store_status<V>(a.o.status + v * V, worst);
     }
-  }
-  if (V > 1 && blockIdx.x == a.o.tail) {
-    const int64_t i = a.o.nvec * V + threadIdx.x;
-    if (i < a.o.n) {
-      T prod = T(1);
-      int worst = 0;
-      for (int b = 0; b < a.k; ++b) {
-        T zz[9], xx[9], dt;
+    if (V > 1 && tile == a.o.tiles - 1) {
+      const int64_t i = a.o.nvec * V + threadIdx.x;
+      if (i < a.o.n) {
+        T prod = T(1);
+        int worst = 0;
+        for (int b = 0; b < a.k; ++b) {
+          T zz[9], xx[9], dt;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) zz[k] = Z[(int64_t)(9 * b + k) * a.o.zp + i];
-        const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
-        prod *= dt;
-        worst = st > worst ? st : worst;
-        if (a.o.inv)
+          for (int k = 0; k < 9; ++k) zz[k] = Z[(int64_t)(9 * b + k) * a.o.zp + i];
+          const int st = run_pixel<T, OP>(zz, xx, dt, a.o.status || a.o.counters);
+          prod *= dt;
+          worst = st > worst ? st : worst;
+          if (a.o.inv)
 #pragma unroll
-          for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[(int64_t)(9 * b + k) * a.o.ip + i] = xx[k];
-        if (a.bdet) ((T*)a.bdet)[(int64_t)b * a.bp + i] = dt;
+            for (int k = 0; k < 9; ++k) ((T*)a.o.inv)[(int64_t)(9 * b + k) * a.o.ip + i] = xx[k];
+          if (a.bdet) ((T*)a.bdet)[(int64_t)b * a.bp + i] = dt;
+        }
+        tally(worst, c0, c1, c2);
+        if (a.o.det) ((T*)a.o.det)[i] = prod;
+        if (a.o.status) a.o.status[i] = (uint8_t)worst;
       }
-      tally(worst, c0, c1, c2);
-      if (a.o.det) ((T*)a.o.det)[i] = prod;
-      if (a.o.status) a.o.status[i] = (uint8_t)worst;
     }
   }
   if (a.o.counters) flush_counters(a.o.counters, c0, c1, c2);
@@ -581,6 +596,19 @@ polsar_launch inv_det_cfg(int64_t n, int dtype, int method, int prec, bool want_
   return c;
 }
 
+// The multilook's launch.  FP32 compensated with Z stored too: one block per CU
+// fewer than the table's for its 9 more write streams, from four looks on
+// (3000x3001, four looks: 272 us at 5, 277 at 6; 4096x4096: 464 and 470; nine
+// looks of 2000x2000: 204 and 207), below which the looks' loads are too few to
+// hide the arithmetic (two of 2000x2000: 100 and 94).
+polsar_launch multilook_cfg(int dtype, int method, int prec, int n_looks, bool want_z) {
+  polsar_launch c = get_cfg(2, dtype, method, prec);
+  if (want_z && n_looks >= 4 && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED &&
+      c.blocks_per_cu > 1)
+    --c.blocks_per_cu;
+  return c;
+}
+
 // The Wishart kernel's launch.  A pass that writes no gradient runs twice the
 // resident blocks of the table: the cap is there for the nine write streams,
 // and a pass without them is bound by its reads in flight (forward alone,
@@ -779,7 +807,6 @@ hipError_t dispatch_block_v(const polsar_launch& c, BlockArgs& a, hipStream_t s)
   a.o.nvec = a.o.n / V;
   a.o.tiles = std::max<int64_t>(1, (a.o.nvec + c.block - 1) / c.block);
   const int64_t grid = launch_grid(c, a.o.tiles, a.o.counters != nullptr);
-  a.o.tail = (a.o.tiles - 1) % grid;
   const size_t lds = launch_lds(c, 0);
   if (c.nontemporal)
     hipLaunchKernelGGL((k_blockdiag<T, OP, V, true>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
@@ -946,7 +973,7 @@ int polsar_multilook_inv_det(int dtype, int method, int precision, int64_t n, in
   if (n == 0) return POLSAR_OK;
   MultilookArgs a{looks, looks_pitch, n_looks, 1.0 / n_looks, z, z_pitch,
                   InvDetArgs{nullptr, 0, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
-  const polsar_launch c = get_cfg(2, dtype, method, precision);
+  const polsar_launch c = multilook_cfg(dtype, method, precision, n_looks, z != nullptr);
   if (launch_multilook(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
