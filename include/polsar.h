@@ -307,7 +307,11 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *                queue; 1 where that queue would pass 64 KB of LDS)
  *   grid_per_cu  0 = one tile per block; k > 0 = persistent grid of k blocks
  *                per compute unit striding over tiles
- *   nontemporal  1 = streaming (non-temporal) loads and stores
+ *   nontemporal  1 = streaming (non-temporal) stores and loads, but for loads
+ *                of small inputs (ops 0 and 6: 48 MB of planes, 192 MB where
+ *                they do not start on 128-byte lines; ops 1 and 5, calls that
+ *                write a gradient: 192 MB of sigma and Z) and stores of a
+ *                gradient of at most 192 MB in planes that do not start on lines
  *   vector_bytes 16 or 8: bytes per lane per plane access
  *   blocks_per_cu 0 = as many resident blocks as registers allow; k > 0 = at
  *                most k blocks resident per compute unit (enforced by padding

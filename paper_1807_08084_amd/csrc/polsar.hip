@@ -57,6 +57,9 @@ __device__ __forceinline__ void store_vec(const InvDetArgs& a, const T (&out)[9]
   if (a.status) store_status<V>(a.status + e, st);
 }
 
+// Which accesses of a kernel are non-temporal.
+enum : int { LOADS_NT = 1, STORES_NT = 2 };
+
 // Largest dynamic LDS a launch asks for.
 constexpr size_t MAX_DYN_LDS = 64 << 10;
 
@@ -92,8 +95,10 @@ __device__ __forceinline__ void inv_det_vec(const InvDetArgs& a, const T (&in)[9
 template <class T, int OP>
 constexpr bool TAIL_AFTER = OP == ADJ_COMP && std::is_same<T, float>::value;
 
-template <class T, int OP, int V, int U, bool NT>
+// M: LOADS_NT | STORES_NT.
+template <class T, int OP, int V, int U, int M>
 __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4 : 1) void k_inv_det(InvDetArgs a) {
+  constexpr bool LNT = M & LOADS_NT, NT = M & STORES_NT;
   const T* __restrict__ z = (const T*)a.z;
   const int B = blockDim.x;
   unsigned c0 = 0, c1 = 0, c2 = 0;
@@ -126,7 +131,7 @@ __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4
       for (int u = 0; u < U; ++u) valid[u] = v0 + (int64_t)u * B < a.nvec;
       auto load = [&](int u, float (&in)[9][V]) {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) load_v<float, V, NT>(z + k * a.zp + (v0 + (int64_t)u * B) * V, in[k]);
+        for (int k = 0; k < 9; ++k) load_v<float, V, LNT>(z + k * a.zp + (v0 + (int64_t)u * B) * V, in[k]);
       };
       float out[U][9][V], dt[U][V];
       int st[U][V];
@@ -145,7 +150,7 @@ __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4
         const int64_t v = v0 + (int64_t)u * B;
         if (v < a.nvec) {
 #pragma unroll
-          for (int k = 0; k < 9; ++k) load_v<T, V, NT>(z + k * a.zp + v * V, in[u][k]);
+          for (int k = 0; k < 9; ++k) load_v<T, V, LNT>(z + k * a.zp + v * V, in[u][k]);
         }
       }
 #pragma unroll
@@ -387,8 +392,9 @@ __device__ __forceinline__ double wishart_vec(const WishartArgs& a, const T (&s)
   return acc;
 }
 
-template <class T, int V, int U, bool NT>
+template <class T, int V, int U, int M>
 __global__ __launch_bounds__(256) void k_wishart(WishartArgs a) {
+  constexpr bool LNT = M & LOADS_NT, NT = M & STORES_NT;
   const T* __restrict__ S = (const T*)a.s;
   const T* __restrict__ Z = (const T*)a.z;
   const int B = blockDim.x;
@@ -402,9 +408,9 @@ __global__ __launch_bounds__(256) void k_wishart(WishartArgs a) {
       const int64_t v = v0 + (int64_t)u * B;
       if (v < a.nvec) {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) load_v<T, V, NT>(S + k * a.sp + v * V, s[u][k]);
+        for (int k = 0; k < 9; ++k) load_v<T, V, LNT>(S + k * a.sp + v * V, s[u][k]);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) load_v<T, V, NT>(Z + k * a.zp + v * V, z[u][k]);
+        for (int k = 0; k < 9; ++k) load_v<T, V, LNT>(Z + k * a.zp + v * V, z[u][k]);
       }
     }
     double acc = 0.0;
@@ -658,15 +664,34 @@ int64_t launch_grid(const polsar_launch& c, int64_t tiles, bool counters) {
   return grid;
 }
 
-// Launch helpers: pick the template instance for (V, U, NT).
+// Non-temporal accesses of a launch that asks for them.  Loads of inputs that
+// the 256 MB memory-side cache holds go through it.  us with streaming and with
+// cached loads, over six images in turn (and over one, read before): FP32
+// inverse, 1048576 pixels 19.4, 15.9 (17.6, 15.0); in planes that do not start
+// on lines, so that two waves read a line, 5469354: 76.6, 75.1 (74.9, 63.1); in
+// aligned planes, past 48 MB, streaming loads stay: 4194304: 63.4, 64.9 (62.0,
+// 48.5).  Past 192 MB both lose: 12000000, 149.9 and 153.5.  Wishart, FP32, sigma
+// and Z together: 1984267 pixels: backward 37.9, 36.9 (37.4, 35.1), fused 43.7,
+// 42.7 (42.6, 39.6); 5469354, past the line: fused 107, 111; forward alone gains
+// nothing (FP64, 524288 pixels: 20.1, 19.4, one image 19.1, 21.3).
+constexpr int64_t CACHED_BYTES = int64_t(192) << 20, CACHED_ALIGNED = int64_t(48) << 20;
+bool off_lines(const void* p, int64_t pitch, size_t es) { return (uintptr_t)p % 128 || pitch * (int64_t)es % 128; }
+int access_mode(const polsar_launch& c, bool cached_loads) {
+  return !c.nontemporal ? 0 : cached_loads ? STORES_NT : LOADS_NT | STORES_NT;
+}
+
+// Launch helpers: pick the template instance for (V, U, accesses).
 template <class T, int OP, int V, int U>
 hipError_t go_inv_det(const polsar_launch& c, int64_t grid, InvDetArgs& a, hipStream_t s) {
   const size_t lds =
       launch_lds(c, (OP == ADJ_COMP && std::is_same<T, float>::value) ? comp_queue_bytes(c.block, U * V) : 0);
-  if (c.nontemporal)
-    hipLaunchKernelGGL((k_inv_det<T, OP, V, U, true>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
-  else
-    hipLaunchKernelGGL((k_inv_det<T, OP, V, U, false>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
+  const dim3 g((unsigned)grid), b(c.block);
+  const int64_t bytes = 9 * a.n * (int64_t)sizeof(T);
+  switch (access_mode(c, bytes <= (off_lines(a.z, a.zp, sizeof(T)) ? CACHED_BYTES : CACHED_ALIGNED))) {
+    case 0: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, 0>), g, b, lds, s, a); break;
+    case STORES_NT: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, STORES_NT>), g, b, lds, s, a); break;
+    default: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, LOADS_NT | STORES_NT>), g, b, lds, s, a); break;
+  }
   return hipGetLastError();
 }
 
@@ -843,10 +868,20 @@ hipError_t launch_block(int dtype, int op, const polsar_launch& c, BlockArgs& a,
 template <class T, int V, int U>
 hipError_t go_wishart(const polsar_launch& c, int64_t grid, WishartArgs& a, hipStream_t s) {
   const size_t lds = launch_lds(c, 0);
-  if (c.nontemporal)
-    hipLaunchKernelGGL((k_wishart<T, V, U, true>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
-  else
-    hipLaunchKernelGGL((k_wishart<T, V, U, false>), dim3((unsigned)grid), dim3(c.block), lds, s, a);
+  const dim3 g((unsigned)grid), b(c.block);
+  const int64_t bytes = 9 * a.n * (int64_t)sizeof(T);
+  int m = access_mode(c, a.bwd && 2 * bytes <= CACHED_BYTES);
+  // Two waves' stores into a line of a gradient whose planes do not start on
+  // lines meet in the memory-side cache where it holds the gradient; streaming
+  // ones reach memory as two partial writes (FP32 backward, 5469354 pixels: 113
+  // us streaming, 95 cached; 16777217, past the cache: 313 and 358).
+  if (a.bwd && bytes <= CACHED_BYTES && off_lines(a.grad, a.gp, sizeof(T))) m &= ~STORES_NT;
+  switch (m) {
+    case 0: hipLaunchKernelGGL((k_wishart<T, V, U, 0>), g, b, lds, s, a); break;
+    case LOADS_NT: hipLaunchKernelGGL((k_wishart<T, V, U, LOADS_NT>), g, b, lds, s, a); break;
+    case STORES_NT: hipLaunchKernelGGL((k_wishart<T, V, U, STORES_NT>), g, b, lds, s, a); break;
+    default: hipLaunchKernelGGL((k_wishart<T, V, U, LOADS_NT | STORES_NT>), g, b, lds, s, a); break;
+  }
   return hipGetLastError();
 }
 
