@@ -18,7 +18,7 @@ def _bits(a):
     return a.contiguous().view(torch.int64 if a.dtype == torch.float64 else torch.int32)
 
 
-# strip heights 4, 8, 16, 24, 32 and 64 are taken by some of these (256 compute units)
+# short and tall strips, one and several rounds of them (256 compute units)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
 @pytest.mark.parametrize("H,W,r", [(300, 64, 1), (303, 96, 2), (1025, 1024, 3), (1500, 2049, 1), (2050, 2048, 2),
                                    (3001, 2944, 3), (4100, 3000, 1), (5000, 4096, 1)])
