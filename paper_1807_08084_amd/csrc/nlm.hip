@@ -59,26 +59,9 @@ template <class T> __device__ __forceinline__ T log2_(T x);
 template <> __device__ __forceinline__ float log2_(float x) { return log2f(x); }
 template <> __device__ __forceinline__ double log2_(double x) { return log2(x); }
 
-// Adjugate planes and determinant of a packed FP32 matrix, formed in FP64,
-// where its products are exact, and rounded once.
-__device__ __forceinline__ void adjugate_det(const float* z, float* adj, float& det) {
-  double zd[9], c[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) zd[k] = (double)z[k];
-  px::cofactors_plain(zd, c);
-#pragma unroll
-  for (int k = 0; k < 9; ++k) adj[k] = (float)c[k];
-  det = (float)px::det_from_cofactors(zd, c);
-}
-
 // DIST 0: symmetrized Kullback-Leibler, one chain of 18 FMAs over Z and Z^-1
-// of both pixels.  DIST 1: Bhattacharyya; in FP32 the determinant of the pair's
-// sum is taken by multilinearity,
-//   det(P + Q) = det P + det Q + tr(adj(P) Q) + tr(adj(Q) P),
-// with each pixel's adjugate formed once (in FP64, so that only its rounding
-// is left): 20 operations per pair where the sum's own cofactors take 29, and
-// an error against 64 bits of 2.5-4.8e-7 where those had 5-29e-7 (images of
-// 37x70 to 1024x1024, radius 2 to 11).  FP64 keeps the sum's cofactors.
+// of both pixels.  DIST 1: Bhattacharyya, the determinant of the pair's sum by
+// the sum's own cofactors of row 0, in the storage type.
 //
 // Bound by VALU issue: two waves of a SIMD issue FP32 operations in
 // alternation, so a neighbour costs about 2.5 cycles per operation and wave
@@ -93,10 +76,10 @@ __device__ __forceinline__ void adjugate_det(const float* z, float* adj, float& 
 // units' rate.
 template <class T, int DIST, int G, int S>
 __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
-  constexpr bool MIX = DIST == 1 && std::is_same<T, float>::value;
-  // staged values per pixel: Z, then Z^-1 (KL), or adj Z, det Z and its
-  // logarithm (MIX), or the logarithm; and the features an output keeps
-  constexpr int F = DIST == 0 ? 18 : MIX ? 20 : 10, NP = DIST == 0 || MIX ? 18 : 9;
+  // staged values per pixel: Z, then Z^-1 (KL) or the logarithm of det Z (B);
+  // and the features an output keeps
+  constexpr int F = DIST == 0 ? 18 : 10, NP = DIST == 0 ? 18 : 9;
+  constexpr bool BARE = DIST == 1 && std::is_same<T, float>::value;  // the hardware's logarithm, below
   constexpr int E = 16 / sizeof(T), FQ = (F + E - 1) / E;  // values per 16-byte LDS access
   typedef T VT __attribute__((ext_vector_type(E)));
   // a compile-time row length keeps every access at a fixed offset from one
@@ -120,37 +103,25 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
   const T alpha = DIST == 0 ? -N * log2e / (T(2) * (T)a.h) : -N / (T)a.h;
   const T beta = DIST == 0 ? T(3) * N * log2e / (T)a.h : T(3) * N / (T)a.h;
 
-  // the outputs' features: Z_p with the off-diagonal doubled (for tr(Q^-1 P)
-  // and tr(adj(Q) P)), then Z_p^-1 or adj Z_p likewise; FP64 B: Z_p itself.
-  // lp: log2 det Z_p, in MIX its part of the exponent
-  T P[G][NP], detp[G], lp[G], acc[G][9], ws[G];
+  // the outputs' features: KL: Z_p with the off-diagonal doubled (for
+  // tr(Q^-1 P)), then Z_p^-1 likewise; B: Z_p, and log2 det Z_p in lp
+  T P[G][NP], lp[G], acc[G][9], ws[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    ws[g] = detp[g] = lp[g] = T(0);
+    ws[g] = lp[g] = T(0);
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[g][k] = T(0);
 #pragma unroll
     for (int k = 0; k < NP; ++k) P[g][k] = T(0);
     if (px < a.W && y0 + g < a.H) {
       const int64_t i = (y0 + g) * a.W + px;
-      T z[9];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        z[k] = Z[k * a.zp + i];
-        P[g][k] = NP == 18 ? z[k] * (k < 3 ? T(1) : T(2)) : z[k];
-      }
+      for (int k = 0; k < 9; ++k) P[g][k] = Z[k * a.zp + i] * (DIST == 1 || k < 3 ? T(1) : T(2));
       if constexpr (DIST == 0) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) P[g][9 + k] = A[k * a.ap + i] * (k < 3 ? T(1) : T(2));
       } else {
         lp[g] = log2_(A[i]);
-        if constexpr (MIX) {
-          lp[g] = fma(T(-0.5) * alpha, lp[g], beta);
-          T adj[9];
-          adjugate_det(z, adj, detp[g]);
-#pragma unroll
-          for (int k = 0; k < 9; ++k) P[g][9 + k] = adj[k] * (k < 3 ? T(1) : T(2));
-        }
       }
     }
   }
@@ -182,14 +153,6 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
         tt = fma(q[9 + k], P[g][k], tt);
       }
       return tt;
-    } else if constexpr (MIX) {
-      T tt = detp[g] + q[18];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        tt = fma(P[g][9 + k], q[k], tt);
-        tt = fma(q[9 + k], P[g][k], tt);
-      }
-      return tt;
     } else {
       T mm[9], cf[9];
 #pragma unroll
@@ -198,29 +161,28 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
       return px::det_from_cofactors(mm, cf);
     }
   };
-  // tt: the score, in MIX its logarithm
+  // tt: the score, in FP32 B its logarithm
   auto accumulate = [&](int g, T tt, const T (&q)[F]) {
     T w;
     if constexpr (DIST == 0) w = exp2_(alpha * tt + beta);
-    else if constexpr (MIX) w = exp2_(fma(alpha, tt, lp[g] + q[19]));
-    else w = exp2_(alpha * (log2_(tt) - T(0.5) * (lp[g] + q[9])) + beta);
+    else w = exp2_(alpha * ((BARE ? tt : log2_(tt)) - T(0.5) * (lp[g] + q[9])) + beta);
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[g][k] += w * q[k];
     ws[g] += w;
   };
   // A neighbour against the outputs [lo, hi].  log2f is the hardware's
   // logarithm but for subnormal numbers, which it scales first: 5 operations a
-  // pair that are left to waves that meet one (B, FP32, 2048x2048, r = 7: 951 ->
-  // 920 us; 256x256, r = 11: 52 -> 48).
+  // pair that are left to waves that meet one (B, FP32, with the inverse before
+  // it: 2048x2048, r = 7: 1086 -> 1061 us; 450x600, r = 5: 54 -> 50).
   auto neighbour = [&](int lo, int hi, const T (&q)[F]) {
     T tt[G];
     bool small = false;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       tt[g] = score(g, q);
-      if constexpr (MIX) small |= tt[g] < T(1.17549435e-38f);
+      if constexpr (BARE) small |= tt[g] < T(1.17549435e-38f);
     }
-    if constexpr (MIX) {
+    if constexpr (BARE) {
       T lg[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) lg[g] = __builtin_amdgcn_logf(tt[g]);
@@ -255,10 +217,6 @@ __global__ __launch_bounds__(TW * S) void k_nlm(NlmArgs a) {
         for (int k = 0; k < 9; ++k) v[9 + k] = A[k * a.ap + i];
       } else {
         v[F - 1] = log2_(A[i]);
-        if constexpr (MIX) {
-          adjugate_det(v, v + 9, v[18]);
-          v[F - 1] *= T(-0.5) * alpha;
-        }
       }
 #pragma unroll
       for (int k = F; k < FQ * E; ++k) v[k] = T(0);
@@ -343,9 +301,9 @@ void go_nlm(const NlmArgs& a, hipStream_t s) {
 // tiles): 39 us (2, 8), 49 (2, 4), 151 (2, 1); 450x600, r = 5 (2250 tiles):
 // 46 us (2, 4), 54 (2, 8), 62 (2, 1); 1024x1024, r = 11 (8192): 445 us (2, 4),
 // 436 (3, 4), 490 (3, 1); 1200x1200, r = 5 (11400): 181 us (3, 1), 183 (2, 4);
-// 2048x2048, r = 11: 1607 us (3, 1), 1705 (2, 4).  Three rows only there: B
-// in FP32 ran 2.06 ms with two and 2.09 with three, FP64 has no registers for
-// three.
+// 2048x2048, r = 11: 1607 us (3, 1), 1705 (2, 4).  Three rows only there: B in
+// FP32, with the inverse before it, takes 1062 us with two and 1088 with three
+// (2048x2048, r = 7; 450x600, r = 5: 51 and 57), FP64 has no registers for three.
 template <class T, int DIST>
 void launch_nlm(const NlmArgs& a, hipStream_t s) {
   const int64_t tiles = ((a.W + TW - 1) / TW) * ((a.H + 1) / 2);
