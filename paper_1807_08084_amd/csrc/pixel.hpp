@@ -389,7 +389,8 @@ PX_HD bool adjugate_comp_try(const float z0[9], float* bound_out = nullptr) {
 
 // adjugate_comp_quick: the plain FP64 evaluation, rounded to FP32, and what
 // it settles.  With h = a d f, tr = a + d + f, for positive a, 2x2 minors and
-// det, tr <= 2^40 and det >= 2^-88 (1 + tr):
+// det, tr <= 2^43 and det >= 2^-99 (1 + 2.5 tr), which is within a factor of two
+// of the smallest determinant that the FP32 evaluation carries:
 // * h <= 2^24 det: QUICK_VALUE, the result stands.  With u = 2^-53: the
 //   minors give |e|^2 <= d f and so on, so the products of the cofactors of
 //   row 0 have magnitude sums S_i with M = sum |x_i| S_i <= (4 + 2 sqrt 2) h
@@ -409,9 +410,11 @@ PX_HD bool adjugate_comp_try(const float z0[9], float* bound_out = nullptr) {
 //   rounding errors, |t| and |s| of dot3 at most 2 u S and 3 u S, so
 //   rerr_i <= 8 u S_i; of det_comp, R <= 59 u M and C <= 8 u M; so its bound is
 //   E <= u det + 67 u^2 M + 65 eta (1 + X) with X <= 2.5 tr, at most
-//   (0.6 + 4.3 + 0.01) 1e-7 det: half of REROUTE_REL.  The range keeps every
-//   FP32 product below 2^121 and the diagonal products (each at least det
-//   over the third entry) above 2^-88.
+//   (0.60 + 4.27 + 4.84) 1e-7 det: below REROUTE_REL.  The range keeps every
+//   FP32 sum below 2^127.1 (h <= (tr / 3)^3), the diagonal products (each at
+//   least det over the third entry) above 2^-98, so that none of a d f
+//   underflows, and the minors above 2^-116 and the 22 eta that underflow can
+//   add to one.
 enum : int { QUICK_NONE = 0, QUICK_VALUE = 1, QUICK_ALL = 2 };
 
 PX_HD int adjugate_comp_quick(const float z[9], float x[9], float& det) {
@@ -441,9 +444,9 @@ PX_HD int adjugate_comp_quick(const float z[9], float x[9], float& det) {
   x[7] = (float)(c7 * t);
   x[8] = (float)(c8 * t);
   const float tr = z[0] + z[1] + z[2], h = z[0] * z[1] * z[2];
-  constexpr float lo = 3.2311742677852644e-27f;  // 2^-88
-  const bool ok = (z[0] > 0.0f) & (x[0] > 0.0f) & (x[1] > 0.0f) & (x[2] > 0.0f) & (tr <= 1099511627776.0f) &
-                  (det >= fma_(lo, tr, lo)) & (h <= 16777216.0f * det);
+  constexpr float lo = 1.5777218104420236e-30f;  // 2^-99
+  const bool ok = (z[0] > 0.0f) & (x[0] > 0.0f) & (x[1] > 0.0f) & (x[2] > 0.0f) & (tr <= 8796093022208.0f) &
+                  (det >= lo * fma_(2.5f, tr, 1.0f)) & (h <= 16777216.0f * det);
   return !ok ? QUICK_NONE : h <= 262144.0f * det ? QUICK_ALL : QUICK_VALUE;
 }
 

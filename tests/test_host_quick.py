@@ -97,3 +97,39 @@ def test_quick_form(lib, name):
     assert np.all(oracle.det_rel_err(det[sel], dh, dl) <= tol)
     normal = (np.abs(ih) > 1e-30).all(axis=0) if name == "graded" else np.ones(sel.sum(), bool)
     assert np.all(oracle.inv_rel_err(inv[:, sel], ih, il)[normal] <= tol)
+
+
+# Where FP32 alone carries a well-conditioned matrix, the quick form does too
+# and settles its status, but within a factor of two of the ends of FP32's range.
+@pytest.mark.parametrize("scale", [3e-10, 5e-10, 1e-9, 1.5e-9, 3e-9, 1e-8, 1e-4, 1.0, 1e6, 1e11, 1e12])
+def test_quick_form_carries_well_conditioned_scales(lib, scale):
+    rng = np.random.default_rng(23)
+    s = (rng.standard_normal((20000, 3, 8)) + 1j * rng.standard_normal((20000, 3, 8))) * np.sqrt(0.5)
+    z = synth.pack(np.einsum("mik,mjk->mij", s, np.conj(s)) / 8 * scale)
+    z = np.ascontiguousarray(z.astype(np.float32))
+    inv, det, quick, ok, st, bad = _run(lib, z)
+    assert bad == 0 and ok.mean() >= 0.99
+    assert (quick[ok == 1] == ALL).mean() >= 0.99
+    assert np.all(ok[quick == ALL] == 1) and np.all(st[quick != NONE] == 1)
+    sel = quick != NONE
+    (ih, il), (dh, dl) = oracle.ge128(z[:, sel].astype(np.float64))
+    tol = 9e-8 + 2.0 ** -24
+    assert np.all(oracle.det_rel_err(det[sel], dh, dl) <= tol)
+    assert np.all(oracle.inv_rel_err(inv[:, sel], ih, il) <= tol)
+
+
+# The ends themselves: determinants and traces across both limits, ALL only
+# where the FP32 evaluation carries the pixel.
+@pytest.mark.parametrize("lo,hi", [(-36, -28), (38, 46)])
+def test_quick_form_at_the_ends_of_its_range(lib, lo, hi):
+    rng = np.random.default_rng(31)
+    m = 200000
+    U = synth.haar_unitary(rng, m)
+    eig = np.stack([np.ones(m), 10.0 ** -rng.uniform(0, 3, m), 10.0 ** -rng.uniform(0, 4, m)], 1)
+    with np.errstate(over="ignore", under="ignore"):
+        z = synth.pack(np.einsum("mij,mj,mkj->mik", U, eig, np.conj(U))) * 2.0 ** rng.uniform(lo, hi, m)
+        z = np.ascontiguousarray(z.astype(np.float32))
+    inv, det, quick, ok, st, bad = _run(lib, z)
+    assert bad == 0
+    assert (quick == ALL).any() and (quick == NONE).any() and (ok == 0).any()
+    assert np.all(ok[quick == ALL] == 1) and np.all(st[quick != NONE] == 1)
