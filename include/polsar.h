@@ -308,10 +308,12 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *   grid_per_cu  0 = one tile per block; k > 0 = persistent grid of k blocks
  *                per compute unit striding over tiles
  *   nontemporal  1 = streaming (non-temporal) stores and loads, but for loads
- *                of small inputs (ops 0 and 6: 48 MB of planes, 192 MB where
- *                they do not start on 128-byte lines; ops 1 and 5, calls that
- *                write a gradient: 192 MB of sigma and Z) and stores of a
- *                gradient of at most 192 MB in planes that do not start on lines
+ *                of the inverse's inputs of up to 48 MB, or below 2^25 pixels
+ *                in planes that do not start on 128-byte lines, and, in Wishart
+ *                calls that write a gradient, loads of sigma and Z of up to 80
+ *                MB together or in planes that do not start on lines, and loads
+ *                and stores with 80 to 176 MB of sigma and Z and a gradient in
+ *                planes that do not start on lines
  *   vector_bytes 16 or 8: bytes per lane per plane access
  *   blocks_per_cu 0 = as many resident blocks as registers allow; k > 0 = at
  *                most k blocks resident per compute unit (enforced by padding

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/polsar.h"
+#include "access.hpp"
 #include "common.hpp"
 #include "host.hpp"
 
@@ -56,9 +57,6 @@ __device__ __forceinline__ void store_vec(const InvDetArgs& a, const T (&out)[9]
   if (a.det) store_v<T, V, NT>((T*)a.det + e, dt);
   if (a.status) store_status<V>(a.status + e, st);
 }
-
-// Which accesses of a kernel are non-temporal.
-enum : int { LOADS_NT = 1, STORES_NT = 2 };
 
 // Largest dynamic LDS a launch asks for.
 constexpr size_t MAX_DYN_LDS = 64 << 10;
@@ -664,30 +662,13 @@ int64_t launch_grid(const polsar_launch& c, int64_t tiles, bool counters) {
   return grid;
 }
 
-// Non-temporal accesses of a launch that asks for them.  Loads of inputs that
-// the 256 MB memory-side cache holds go through it.  us with streaming and with
-// cached loads, over six images in turn (and over one, read before): FP32
-// inverse, 1048576 pixels 19.4, 15.9 (17.6, 15.0); in planes that do not start
-// on lines, so that two waves read a line, 5469354: 76.6, 75.1 (74.9, 63.1); in
-// aligned planes, past 48 MB, streaming loads stay: 4194304: 63.4, 64.9 (62.0,
-// 48.5).  Past 192 MB both lose: 12000000, 149.9 and 153.5.  Wishart, FP32, sigma
-// and Z together: 1984267 pixels: backward 37.9, 36.9 (37.4, 35.1), fused 43.7,
-// 42.7 (42.6, 39.6); 5469354, past the line: fused 107, 111; forward alone gains
-// nothing (FP64, 524288 pixels: 20.1, 19.4, one image 19.1, 21.3).
-constexpr int64_t CACHED_BYTES = int64_t(192) << 20, CACHED_ALIGNED = int64_t(48) << 20;
-bool off_lines(const void* p, int64_t pitch, size_t es) { return (uintptr_t)p % 128 || pitch * (int64_t)es % 128; }
-int access_mode(const polsar_launch& c, bool cached_loads) {
-  return !c.nontemporal ? 0 : cached_loads ? STORES_NT : LOADS_NT | STORES_NT;
-}
-
 // Launch helpers: pick the template instance for (V, U, accesses).
 template <class T, int OP, int V, int U>
 hipError_t go_inv_det(const polsar_launch& c, int64_t grid, InvDetArgs& a, hipStream_t s) {
   const size_t lds =
       launch_lds(c, (OP == ADJ_COMP && std::is_same<T, float>::value) ? comp_queue_bytes(c.block, U * V) : 0);
   const dim3 g((unsigned)grid), b(c.block);
-  const int64_t bytes = 9 * a.n * (int64_t)sizeof(T);
-  switch (access_mode(c, bytes <= (off_lines(a.z, a.zp, sizeof(T)) ? CACHED_BYTES : CACHED_ALIGNED))) {
+  switch (c.nontemporal ? inv_det_access(a.n, sizeof(T), off_lines(a.z, a.zp, sizeof(T))) : 0) {
     case 0: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, 0>), g, b, lds, s, a); break;
     case STORES_NT: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, STORES_NT>), g, b, lds, s, a); break;
     default: hipLaunchKernelGGL((k_inv_det<T, OP, V, U, LOADS_NT | STORES_NT>), g, b, lds, s, a); break;
@@ -869,16 +850,10 @@ template <class T, int V, int U>
 hipError_t go_wishart(const polsar_launch& c, int64_t grid, WishartArgs& a, hipStream_t s) {
   const size_t lds = launch_lds(c, 0);
   const dim3 g((unsigned)grid), b(c.block);
-  const int64_t bytes = 9 * a.n * (int64_t)sizeof(T);
-  int m = access_mode(c, a.bwd && 2 * bytes <= CACHED_BYTES);
-  // Two waves' stores into a line of a gradient whose planes do not start on
-  // lines meet in the memory-side cache where it holds the gradient; streaming
-  // ones reach memory as two partial writes (FP32 backward, 5469354 pixels: 113
-  // us streaming, 95 cached; 16777217, past the cache: 313 and 358).
-  if (a.bwd && bytes <= CACHED_BYTES && off_lines(a.grad, a.gp, sizeof(T))) m &= ~STORES_NT;
-  switch (m) {
+  const bool off_in = off_lines(a.s, a.sp, sizeof(T)) || off_lines(a.z, a.zp, sizeof(T));
+  const bool off_grad = a.bwd && off_lines(a.grad, a.gp, sizeof(T));
+  switch (c.nontemporal ? wishart_access(a.n, sizeof(T), a.bwd, off_in, off_grad) : 0) {
     case 0: hipLaunchKernelGGL((k_wishart<T, V, U, 0>), g, b, lds, s, a); break;
-    case LOADS_NT: hipLaunchKernelGGL((k_wishart<T, V, U, LOADS_NT>), g, b, lds, s, a); break;
     case STORES_NT: hipLaunchKernelGGL((k_wishart<T, V, U, STORES_NT>), g, b, lds, s, a); break;
     default: hipLaunchKernelGGL((k_wishart<T, V, U, LOADS_NT | STORES_NT>), g, b, lds, s, a); break;
   }
