@@ -15,9 +15,6 @@
 
 #include <algorithm>
 #include <cstring>
-#include <map>
-#include <mutex>
-#include <tuple>
 #include <type_traits>
 #include <vector>
 
@@ -25,6 +22,7 @@
 #include "access.hpp"
 #include "common.hpp"
 #include "host.hpp"
+#include "launch.hpp"
 
 namespace {
 using namespace polsar_dev;
@@ -488,76 +486,7 @@ __global__ __launch_bounds__(256) void k_copy(const T* __restrict__ src, int64_t
 }
 
 // ------------------------------------------------------------------ host side
-std::mutex g_mu;
-std::map<std::tuple<int, int, int, int>, polsar_launch> g_cfg;
-
-// Defaults from a sweep of all launch shapes on MI355X (4096x4096 image):
-// one 128-lane tile per block, one 128-bit vector per lane per plane,
-// non-temporal (streaming) loads and stores.
-// The Wishart kernel in FP64 with 16-byte accesses needs all 256 VGPRs (one
-// wave per SIMD); with 8-byte accesses it runs at three waves per SIMD and
-// 20% faster.  blocks_per_cu caps the resident blocks: with 4-5 waves per CU
-// the 19 concurrent plane streams of a 3x3 inverse reach ~82% of HBM peak,
-// with more they contend.
-// Images below this many pixels take the Wishart kernel's launch from op 5
-// of the table instead of op 1: on 2048x2048 (2^22 pixels) 8-byte accesses
-// in 128-lane blocks, at most 5 per CU, ran the FP32 fused forward+backward
-// 9-16% faster than the 4096x4096 image's shape, which is 4% faster there.
-constexpr int64_t WISHART_SMALL = int64_t(1) << 23;
-// Images of at least this many pixels take the inverse kernel's launch from
-// op 6 of the table instead of op 0.  FP32 compensated on 8192x8192: 16-byte
-// accesses in 128-lane blocks, at most 4 per CU: 846 us with a quarter of the
-// pixels past the quick form, 841 with almost none (8-byte accesses, at most 6
-// per CU: 866 and 845; on 4096x4096 images those take 204 us against 209).
-// The Cholesky forms and the FP32-I/O FP64
-// adjugate take the joint best of both 8192x8192 images (1-2% over their
-// op-0 shapes); the other forms keep their op-0 shapes.
-constexpr int64_t INV_DET_LARGE = int64_t(1) << 25;
-
-polsar_launch default_launch(int op, int dtype, int method, int prec) {
-  const bool f64 = dtype == POLSAR_F64, chol = method == POLSAR_CHOLESKY;
-  switch (op) {
-    case 1:  // FP32: 8-byte accesses, at most 4 blocks per CU (4096^2: 0.774 of HBM against 0.763 with
-             // 16-byte accesses and no cap; 8192^2: 0.738 against 0.684).  FP64 shapes with 256-lane blocks
-             // reach 0.78 on 4096^2 but fall to 0.58 on 8192^2; 128 lanes, 4 per CU: 0.754 and 0.685
-      return f64 ? polsar_launch{128, 1, 0, 1, 8, 4} : polsar_launch{256, 1, 0, 1, 8, 4};
-    case 5:  // the Wishart kernel below WISHART_SMALL pixels: more, smaller tiles (FP64 on 2048^2: 5 blocks
-             // per CU 0.757 of HBM, the Wishart tuner's pick in every bench run, against 0.689 with 4)
-      return f64 ? polsar_launch{128, 1, 0, 1, 8, 5} : polsar_launch{128, 1, 0, 1, 8, 5};
-    case 2:  // FP32 compensated: 8-byte accesses, at most 6 blocks of 128 lanes per CU (four-look 4096x4096
-             // image: 357 us, 370 with 8 blocks of 256 lanes)
-      if (!f64 && !chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 8, 6};
-      return f64 ? polsar_launch{256, 1, 0, 1, 8, 4} : polsar_launch{128, 1, 0, 1, 16, 0};
-    case 3:  // one block of 128 lanes per tile, 8-byte accesses.  FP32, 12 images of 128..2048 and of 1024..2048
-             // a side: 219 and 614 us at 6 blocks per CU, 221 and 624 without a cap.  FP64, 12 images of 128..1024
-             // and of 1024 a side: 156 and 697 us at 5, 154 and 748 at 6; a persistent grid of 2 blocks of 256
-             // lanes, 169 and 844
-      return f64 ? polsar_launch{128, 1, 0, 1, 8, 5} : polsar_launch{128, 1, 0, 1, 8, 6};
-    case 4:  // copy probe: few waves in flight stream best
-      return polsar_launch{64, 1, 0, 1, 16, 5};
-    case 6:  // the inverse kernel on images of at least INV_DET_LARGE pixels
-      if (f64) break;
-      if (!chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 16, 4};
-      if (!chol && prec == POLSAR_WIDE) return polsar_launch{64, 1, 0, 1, 16, 5};
-      if (chol && prec == POLSAR_PLAIN) return polsar_launch{128, 1, 0, 1, 16, 3};
-      if (chol && prec == POLSAR_COMPENSATED) return polsar_launch{128, 1, 0, 1, 16, 8};
-      break;
-    default:
-      break;
-  }
-  // op 0: winners of the autotuner on 4096x4096 and 8192x8192 images of the
-  // same recipe, taken together.  FP32 compensated, 4096x4096: 204-207 us with
-  // at most 6 blocks of 128 lanes of 8-byte accesses, without and with
-  // statuses, 210 and 211 with 8.  The FP64 adjugate runs 11%
-  // faster on 8192x8192 with 16-byte accesses and 6 single-wave blocks per
-  // CU than with 12 waves of 8-byte accesses (1% slower on 4096x4096).
-  if (!chol && prec == POLSAR_COMPENSATED) return f64 ? polsar_launch{64, 1, 0, 1, 16, 6} : polsar_launch{128, 1, 0, 1, 8, 6};
-  if (chol && prec == POLSAR_PLAIN) return f64 ? polsar_launch{64, 1, 0, 1, 16, 5} : polsar_launch{256, 1, 0, 1, 8, 3};
-  if (!chol && prec == POLSAR_PLAIN) return f64 ? polsar_launch{64, 1, 0, 1, 16, 6} : polsar_launch{64, 1, 0, 1, 16, 5};
-  if (chol && prec == POLSAR_WIDE) return polsar_launch{64, 2, 0, 1, 16, 0};
-  if (chol) return polsar_launch{64, 1, 0, 1, 16, 0};
-  return polsar_launch{128, 1, 0, 1, 8, 0};  // adjugate, FP32 storage with FP64 arithmetic
-}
+LaunchTable g_table;
 
 // Dynamic LDS bytes for a launch: what the kernel needs, raised so that at
 // most blocks_per_cu blocks fit in a compute unit's LDS.
@@ -579,63 +508,6 @@ size_t launch_lds(const polsar_launch& c, size_t need) {
   size_t pad = (size_t)lds_per_cu() / (size_t)(c.blocks_per_cu + 1) + 1024;
   pad = std::min<size_t>(pad, MAX_DYN_LDS);
   return std::max(need, pad);
-}
-
-polsar_launch get_cfg(int op, int dtype, int method, int prec) {
-  std::lock_guard<std::mutex> g(g_mu);
-  auto it = g_cfg.find(std::make_tuple(op, dtype, method, prec));
-  return it == g_cfg.end() ? default_launch(op, dtype, method, prec) : it->second;
-}
-
-// The inverse's launch.  An FP32 compensated call on a large image that wants
-// statuses (op 6) runs twice the resident blocks of the table: the FP32
-// evaluations of its ill-conditioned pixels need the waves (8192x8192 with
-// eigenvalues down to 1e-8: 858 us at 8 blocks per CU, 915 at 5), without
-// them fewer stream better (846 us at 4, 912 at 8).
-polsar_launch inv_det_cfg(int64_t n, int dtype, int method, int prec, bool want_st) {
-  const int op = polsar_inv_det_launch_op(n);
-  polsar_launch c = get_cfg(op, dtype, method, prec);
-  if (op == 6 && want_st && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED)
-    c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
-  return c;
-}
-
-// The multilook's launch.  FP32 compensated with Z stored too: one block per CU
-// fewer than the table's for its 9 more write streams, from four looks on
-// (3000x3001, four looks: 272 us at 5, 277 at 6; 4096x4096: 464 and 470; nine
-// looks of 2000x2000: 204 and 207), below which the looks' loads are too few to
-// hide the arithmetic (two of 2000x2000: 100 and 94).
-polsar_launch multilook_cfg(int dtype, int method, int prec, int n_looks, bool want_z) {
-  polsar_launch c = get_cfg(2, dtype, method, prec);
-  if (want_z && n_looks >= 4 && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED &&
-      c.blocks_per_cu > 1)
-    --c.blocks_per_cu;
-  return c;
-}
-
-// The Wishart kernel's launch.  A pass that writes no gradient runs twice the
-// resident blocks of the table: the cap is there for the nine write streams,
-// and a pass without them is bound by its reads in flight (forward alone,
-// FP32 2048x2048: 57 us, 65 with the table's 5; FP64 4096x4096: 359 with 8,
-// 428 with 4).  The
-// tiles stay those of the table, so the partial sums and the loss have the
-// same bits as the fused pass's.
-polsar_launch wishart_cfg(int64_t n, int dtype, bool bwd) {
-  polsar_launch c = get_cfg(polsar_wishart_launch_op(n), dtype, 0, 0);
-  if (!bwd) c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
-  return c;
-}
-
-bool valid_launch(const polsar_launch& c, int op) {
-  if (c.block != 64 && c.block != 128 && c.block != 256) return false;
-  if (c.unroll != 1 && c.unroll != 2 && !((op == 0 || op == 6) && c.unroll == 4)) return false;
-  if ((op == 2 || op == 3 || op == 4) && c.unroll != 1) return false;
-  if (op == 4 && c.grid_per_cu != 0) return false;
-  if (c.grid_per_cu < 0 || c.grid_per_cu > 64) return false;
-  if (c.nontemporal != 0 && c.nontemporal != 1) return false;
-  if (c.vector_bytes != 16 && c.vector_bytes != 8) return false;
-  if (c.blocks_per_cu < 0 || c.blocks_per_cu > 64) return false;
-  return true;
 }
 
 int device_cus() {
@@ -927,20 +799,19 @@ int polsar_device_compute_units(int* cus) {
   return POLSAR_OK;
 }
 
-int polsar_wishart_launch_op(int64_t n) { return n < WISHART_SMALL ? 5 : 1; }
+int polsar_wishart_launch_op(int64_t n) { return wishart_op(n); }
 
-int polsar_inv_det_launch_op(int64_t n) { return n >= INV_DET_LARGE ? 6 : 0; }
+int polsar_inv_det_launch_op(int64_t n) { return inv_det_op(n); }
 
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out) {
   if (!out || op < 0 || op > 6) return POLSAR_E_ARG;
-  *out = get_cfg(op, dtype, method, precision);
+  *out = g_table.get(op, dtype, method, precision);
   return POLSAR_OK;
 }
 
 int polsar_set_launch(int op, int dtype, int method, int precision, const polsar_launch* cfg) {
   if (!cfg || op < 0 || op > 6 || !valid_launch(*cfg, op)) return POLSAR_E_ARG;
-  std::lock_guard<std::mutex> g(g_mu);
-  g_cfg[std::make_tuple(op, dtype, method, precision)] = *cfg;
+  g_table.set(op, dtype, method, precision, *cfg);
   return POLSAR_OK;
 }
 
@@ -950,7 +821,7 @@ int polsar_inv_det(int dtype, int method, int precision, int64_t n, const void* 
   int r = prepare_inv_det(dtype, method, precision, n, z, z_pitch, inv, inv_pitch, det, status, counters, a);
   if (r) return r;
   if (n == 0) return POLSAR_OK;
-  const polsar_launch c = inv_det_cfg(n, dtype, method, precision, status || counters);
+  const polsar_launch c = g_table.inv_det(n, dtype, method, precision, status || counters);
   if (launch_inv_det(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
@@ -983,7 +854,7 @@ int polsar_multilook_inv_det(int dtype, int method, int precision, int64_t n, in
   if (n == 0) return POLSAR_OK;
   MultilookArgs a{looks, looks_pitch, n_looks, 1.0 / n_looks, z, z_pitch,
                   InvDetArgs{nullptr, 0, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
-  const polsar_launch c = multilook_cfg(dtype, method, precision, n_looks, z != nullptr);
+  const polsar_launch c = g_table.multilook(dtype, method, precision, n_looks, z != nullptr);
   if (launch_multilook(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess)
     return POLSAR_E_HIP;
   return POLSAR_OK;
@@ -1018,7 +889,7 @@ int polsar_blockdiag_inv_det(int dtype, int method, int precision, int64_t n, in
   }
   if (n == 0) return POLSAR_OK;
   BlockArgs a{n_blocks, block_det, block_det_pitch, InvDetArgs{z, z_pitch, inv, inv_pitch, det, status, counters, n, 0, 0, 0}};
-  const polsar_launch c = get_cfg(0, dtype, method, precision);
+  const polsar_launch c = g_table.get(0, dtype, method, precision);
   if (launch_block(dtype, op_code(method, precision), c, a, (hipStream_t)stream) != hipSuccess) return POLSAR_E_HIP;
   return POLSAR_OK;
 }
@@ -1072,7 +943,7 @@ int polsar_wishart_call(int dtype, int pass, int64_t n, const void* sigma, int64
         return POLSAR_E_ALIAS;
     }
   }
-  const polsar_launch c = wishart_cfg(n, dtype, bwd);
+  const polsar_launch c = g_table.wishart(n, dtype, bwd);
   if (fwd && n > 0 && !ws_user) {
     if (wishart_tiles(c, wishart_vector(c, es), n) > ws_words) return POLSAR_E_WORKSPACE;
     if ((r = fixed_ws(&ws))) return r;
@@ -1168,10 +1039,7 @@ int polsar_autotune_inv_det(int dtype, int method, int precision, int64_t n, con
     }
   for (const auto& e : all)
     if (e.first < win_ms) { win_ms = e.first; win = e.second; }
-  {
-    std::lock_guard<std::mutex> g(g_mu);
-    g_cfg[std::make_tuple(polsar_inv_det_launch_op(n), dtype, method, precision)] = win;
-  }
+  g_table.set(inv_det_op(n), dtype, method, precision, win);
   if (best) *best = win;
   if (best_ms) *best_ms = win_ms;
 done:
@@ -1197,7 +1065,7 @@ int polsar_stream_copy(int dtype, int64_t n, const void* src, int64_t src_pitch,
   hipStream_t s = (hipStream_t)stream;
   // launch shape: op 4 of the table (block, access width, non-temporal,
   // resident-block cap); one vector per lane, one tile per block
-  const polsar_launch c = get_cfg(4, dtype, 0, 0);
+  const polsar_launch c = g_table.get(4, dtype, 0, 0);
   const int VW = (int)(c.vector_bytes / es);
   const int64_t nvec = n / VW;
   const int64_t grid = std::max<int64_t>(1, (nvec + c.block - 1) / c.block);
@@ -1307,7 +1175,7 @@ int polsar_streamer_run(polsar_streamer* s, int64_t n, const void* z, int64_t z_
     if (inv && overlap(span(inv, 9, inv_pitch, n, es), rz)) return POLSAR_E_ALIAS;
     if (det && overlap(span(det, 1, n, n, es), rz)) return POLSAR_E_ALIAS;
   }
-  const polsar_launch c = inv_det_cfg(s->chunk, s->dtype, s->method, s->precision, status || counters);
+  const polsar_launch c = g_table.inv_det(s->chunk, s->dtype, s->method, s->precision, status || counters);
   const int op = op_code(s->method, s->precision);
   const size_t P = (size_t)s->pitch * es;
   hipError_t e = hipSuccess;
