@@ -313,6 +313,10 @@ def wishart_loglik(sigma: torch.Tensor, z: torch.Tensor, n_looks: float, *, forw
     return loss, grad, el
 
 
+# bytes of Sigma and Z together up to which the library lets a gradient's stores meet in the memory-side cache
+_GRAD_CACHED = 176 << 20
+
+
 class WishartNLL(torch.autograd.Function):
     """L(S) = sum_px N (ln det S + tr(S^-1 Z)) with the hand-written adjoint.
 
@@ -327,14 +331,21 @@ class WishartNLL(torch.autograd.Function):
         loss, _, _ = wishart_loglik(sigma, z, n_looks, forward=True)
         ctx.save_for_backward(sigma, z)
         ctx.n_looks = float(n_looks)
+        ctx.leaf = sigma.is_leaf
         return loss
 
     @staticmethod
     def backward(ctx, g):
         sigma, z = ctx.saved_tensors
         # contiguous: autograd takes such a gradient over as a leaf's .grad; padded planes it would clone
-        # (FP32 2048x2048: 52 us, more than half of the backward kernel's time)
-        grad = torch.empty(sigma.shape, dtype=sigma.dtype, device=sigma.device)
+        # (FP32 2048x2048: 52 us, more than half of the backward kernel's time).  Nothing is cloned where Sigma
+        # is computed: padded planes there, but for sizes at which the memory-side cache holds contiguous ones
+        # (Sigma = 1.5 theta, step to theta, contiguous and padded: FP32 1537x1537 146 and 156 us, 2501x2499 361
+        # and 353, 8192x8192 3531 and 3503, FP64 2501x2499 737 and 706)
+        if ctx.leaf or 2 * sigma.numel() * sigma.element_size() <= _GRAD_CACHED:
+            grad = torch.empty(sigma.shape, dtype=sigma.dtype, device=sigma.device)
+        else:
+            grad = empty_planes(9, sigma.shape[1:], sigma.dtype, sigma.device)
         wishart_loglik(sigma, z, ctx.n_looks, forward=False, backward=True, grad_loss=g, grad=grad)
         return grad, None, None
 
