@@ -28,6 +28,7 @@
 
 #include "../../include/polsar.h"
 #include "common.hpp"
+#include "nlm_shape.hpp"
 
 namespace {
 using polsar_dev::wave_sync;
@@ -296,21 +297,23 @@ void go_nlm(const NlmArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_nlm<T, DIST, G, S>), grid, dim3(TW * S), 0, s, a);
 }
 
-// Output rows per lane and waves per tile, by the number of two-row tiles
-// (1024 SIMDs to fill).  KL in FP32 as (rows, waves): 256x256, r = 11 (512
-// tiles): 39 us (2, 8), 49 (2, 4), 151 (2, 1); 450x600, r = 5 (2250 tiles):
-// 46 us (2, 4), 54 (2, 8), 62 (2, 1); 1024x1024, r = 11 (8192): 445 us (2, 4),
-// 436 (3, 4), 490 (3, 1); 1200x1200, r = 5 (11400): 181 us (3, 1), 183 (2, 4);
-// 2048x2048, r = 11: 1607 us (3, 1), 1705 (2, 4).  Three rows only there: B in
-// FP32, with the inverse before it, takes 1062 us with two and 1088 with three
-// (2048x2048, r = 7; 450x600, r = 5: 51 and 57), FP64 has no registers for three.
 template <class T, int DIST>
 void launch_nlm(const NlmArgs& a, hipStream_t s) {
-  const int64_t tiles = ((a.W + TW - 1) / TW) * ((a.H + 1) / 2);
-  constexpr int ROWS = DIST == 0 && std::is_same<T, float>::value ? 3 : 2;
-  if (tiles < 1024) go_nlm<T, DIST, 2, 8>(a, s);
-  else if (tiles < 9216) go_nlm<T, DIST, 2, 4>(a, s);
-  else go_nlm<T, DIST, ROWS, 1>(a, s);
+  constexpr bool KL = DIST == 0;
+  if constexpr (std::is_same<T, double>::value) {
+    const polsar_host::NlmShape k = polsar_host::nlm_shape_f64(KL, a.H, a.W, a.r);
+    if (k.rows == 1) {
+      if (k.waves == 1) go_nlm<T, DIST, 1, 1>(a, s);
+      else go_nlm<T, DIST, 1, 4>(a, s);
+    } else if (k.waves == 8) go_nlm<T, DIST, 2, 8>(a, s);
+    else if (k.waves == 4) go_nlm<T, DIST, 2, 4>(a, s);
+    else go_nlm<T, DIST, 2, 1>(a, s);
+  } else {
+    const polsar_host::NlmShape k = polsar_host::nlm_shape(false, KL, a.H, a.W);
+    if (k.waves == 8) go_nlm<T, DIST, 2, 8>(a, s);
+    else if (k.waves == 4) go_nlm<T, DIST, 2, 4>(a, s);
+    else go_nlm<T, DIST, KL ? 3 : 2, 1>(a, s);
+  }
 }
 
 }  // namespace
