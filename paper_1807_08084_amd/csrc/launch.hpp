@@ -124,13 +124,19 @@ class LaunchTable {
   // statuses (op 6) runs twice the resident blocks of the table: the FP32
   // evaluations of its ill-conditioned pixels need the waves (8192x8192 with
   // eigenvalues down to 1e-8: 858 us at 8 blocks per CU, 915 at 5), without
-  // them fewer stream better (846 us at 4, 912 at 8).
+  // them fewer stream better (846 us at 4, 912 at 8).  Between 2^20 and 2^22
+  // pixels one block more does (us at 6 and 7, three images in turn, eigenvalues
+  // down to 1e-8: 1600x1600 41.5, 39.3, 1801x1799 52.0, 49.4; well conditioned
+  // 34.8, 35.2 and 43.5, 43.9); from there on it costs more than it gives where
+  // pixels are well conditioned (2048x2048 65.8, 67.9; 1024x1024 16.2, 16.9).
   polsar_launch inv_det(int64_t n, int dtype, int method, int prec, bool want_st) const {
     const int op = inv_det_op(n);
     bool standard;
     polsar_launch c = get(op, dtype, method, prec, &standard);
-    if (standard && op == 6 && want_st && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED)
-      c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
+    if (standard && want_st && dtype == POLSAR_F32 && method == POLSAR_ADJUGATE && prec == POLSAR_COMPENSATED) {
+      if (op == 6) c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
+      else if (n > int64_t(1) << 20 && n < int64_t(1) << 22) ++c.blocks_per_cu;
+    }
     return c;
   }
 

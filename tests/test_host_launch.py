@@ -62,3 +62,15 @@ def test_calls_without_an_adjustment_take_the_table(lib):
                       (("multilook", (L.F32, L.ADJUGATE, L.COMPENSATED, 4, 0)), (2, L.F32, 0, 1)),
                       (("wishart", (ctypes.c_int64(1 << 20), L.F32, 1)), (5, L.F32, 0, 0))):
         assert _run(lib, call) == _get(lib, key)
+
+
+@pytest.mark.parametrize("n,want_st,more", [(1 << 20, 1, 0), ((1 << 20) + 1, 1, 1), (1801 * 1799, 1, 1), ((1 << 22) - 1, 1, 1),
+                                            (1 << 22, 1, 0), (1801 * 1799, 0, 0)])
+def test_one_more_block_for_statuses_of_middle_sizes(lib, n, want_st, more):
+    key = (0, L.F32, L.ADJUGATE, L.COMPENSATED)
+    default = _get(lib, key)
+    call = ("inv_det", (ctypes.c_int64(n),) + key[1:] + (want_st,))
+    assert _run(lib, call) == dict(default, blocks_per_cu=default["blocks_per_cu"] + more)
+    lib.host_set(*key, ctypes.byref(L.Launch(**dict(default, block=64))))
+    assert _run(lib, call) == dict(default, block=64)
+    lib.host_set(*key, ctypes.byref(L.Launch(**default)))
