@@ -49,7 +49,7 @@ WISHART_BYTES_PER_PX = {"f32": 108, "f64": 216}  # fused fwd+bwd: S, Z in (72) +
 
 
 # the sources the inverse kernel (the step) is compiled from
-STEP_SOURCES = ("common.hpp", "pixel.hpp", "polsar.hip")
+STEP_SOURCES = ("access.hpp", "common.hpp", "launch.hpp", "pixel.hpp", "polsar.hip")
 
 
 def kernel_source_hash() -> str:

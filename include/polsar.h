@@ -60,13 +60,18 @@ typedef enum { POLSAR_ADJUGATE = 0, POLSAR_CHOLESKY = 1 } polsar_method;
 
 /* Arithmetic of one call.
  *   PLAIN        the algorithm in the storage type.
- *   COMPENSATED  ADJUGATE: Dot2-compensated cofactors and determinant (FMA
- *                error-free products and sums); in F32, pixels whose
- *                a-posteriori determinant error bound (a running error
- *                analysis of that evaluation, subnormal results included)
- *                exceeds 1e-6 relative,
- *                or whose det is not positive or not finite, are recomputed
- *                by the compensated F64 path (status POLSAR_PX_REROUTED).
+ *   COMPENSATED  ADJUGATE, F64: Dot2-compensated cofactors and determinant
+ *                (FMA error-free products and sums).
+ *                ADJUGATE, F32: F64 arithmetic on the widened inputs, rounded
+ *                once: plain sums where a d f <= 2^24 det (and det lies in the
+ *                range that F32 arithmetic carries), which leaves F64's error
+ *                below F32's rounding; error-free sums for all other pixels.
+ *                The status says whether F32 arithmetic would have carried the
+ *                pixel: POLSAR_PX_OK where the Dot2-compensated F32 evaluation
+ *                bounds its determinant's error (a running error analysis,
+ *                subnormal results included) by 1e-6 relative,
+ *                POLSAR_PX_REROUTED where it does not, or finds det not
+ *                positive or not finite, and F64 carries the pixel.
  *                CHOLESKY (F32 only): F32, pixels whose pivots fail
  *                recomputed in F64.
  *   WIDE         F32 storage, F64 arithmetic (F32 only). */
@@ -217,11 +222,10 @@ size_t polsar_wishart_workspace_bytes(int dtype, int64_t n);
  * same kernels and launch, so the same results bit for bit.  The call
  * allocates nothing (no hipMalloc, no library allocation).  The forward pass
  * takes at most 2^20 tiles of the launch in use: at the default launches
- * FP32 images of up to 2^28 pixels (2^29 where the planes allow vector
- * accesses) and FP64 images of up to 2^27; beyond that POLSAR_E_WORKSPACE,
- * before any HIP call.  Every call on one GPU shares its array: calls that
- * overlap in time on one GPU (other streams, other host threads) race and
- * must not be issued. */
+ * FP32 images of up to 2^29 pixels and FP64 images of up to 2^27; beyond that
+ * POLSAR_E_WORKSPACE, before any HIP call.  Every call on one GPU shares its
+ * array: calls that overlap in time on one GPU (other streams, other host
+ * threads) race and must not be issued. */
 int polsar_wishart_loglik_noalloc(int dtype, int pass, int64_t n,
                                   const void* sigma, int64_t s_pitch,
                                   const void* z, int64_t z_pitch, double n_looks,
@@ -317,12 +321,14 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *   vector_bytes 16 or 8: bytes per lane per plane access
  *   blocks_per_cu 0 = as many resident blocks as registers allow; k > 0 = at
  *                most k blocks resident per compute unit (enforced by padding
- *                the block's LDS; twice that for FP32 compensated calls of
- *                op 6 that want statuses or counters and for Wishart calls
- *                that write no gradient, one less for FP32 compensated
- *                multilooks of at least 4 looks that store Z).  On MI355X
- *                these streaming kernels move more bytes per second with few
- *                waves in flight per CU. */
+ *                the block's LDS).  On MI355X these streaming kernels move
+ *                more bytes per second with few waves in flight per CU.
+ * An entry that was set or tuned runs as it is.  Of a default entry
+ * blocks_per_cu is doubled for FP32 compensated calls of op 6 that want
+ * statuses or counters and for Wishart calls that write no gradient, one more
+ * for such inverse calls of op 0 between 2^20 and 2^22 pixels, and one less for
+ * FP32 compensated multilooks of at least 4 looks that store Z.
+ * Setting a default entry's own values makes it the default again. */
 typedef struct { int block, unroll, grid_per_cu, nontemporal, vector_bytes, blocks_per_cu; } polsar_launch;
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out);
 int polsar_set_launch(int op, int dtype, int method, int precision, const polsar_launch* cfg);

@@ -7,8 +7,8 @@
 // persistent grid (k blocks per compute unit) that strides over the global
 // tile numbers.  A block finds the image of its first tile by binary search
 // over the images' first tiles and moves forward from there.  Per tile it loads Z once and, as the batch asks, writes the
-// inverse/determinant of Z (FP32 compensated: rejected pixels through the
-// wave's FP64 queue, as in the per-call kernel), then loads S and writes the
+// inverse/determinant of Z (FP32 compensated: what the quick form leaves over
+// through the wave's queue, as in the per-call kernel), then loads S and writes the
 // Wishart term and gradient of S against the same Z.  The descriptor table
 // is a restrict argument (scalar loads) and the plane pointers read from it
 // are typed global, so the accesses are global rather than flat ones.  Wishart partial sums are kept per tile and reduced per
@@ -85,8 +85,8 @@ __device__ __forceinline__ double batch_tile(const BatchArgs& a, const ImgDesc& 
       T out[9][V], dt[V];
       int st[V];
       if constexpr (OP == ADJ_COMP && std::is_same<T, float>::value) {
-        // the FP32 step for the lane's V pixels, rejected pixels through the
-        // wave's shared FP64 queue (as in the per-call kernel)
+        // the quick form for the lane's V pixels, what it leaves over through
+        // the wave's shared queue (as in the per-call kernel)
         extern __shared__ __align__(16) float polsar_dyn_lds[];
         const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
         float* q = polsar_dyn_lds + (size_t)w * 64 * V * QUEUE_WORDS;

@@ -473,8 +473,8 @@ int polsar_boxcar_inv_det(int dtype, int method, int precision, int64_t height, 
   if (height < 0 || width < 0 || radius < 0 || radius > BOX_MAX_R) return POLSAR_E_ARG;
   if (height > ((int64_t)1 << 24) || width > ((int64_t)1 << 24)) return POLSAR_E_ARG;
   const int64_t n = height * width;
-  // one 64-lane block per 64 columns of a strip of at least 4 rows: at most
-  // 2^26 blocks (single columns), a 1-D grid
+  // a block of at most 512 lanes takes at least 64 columns of a strip of at
+  // least 4 rows: a little over 2^24 blocks, a 1-D grid
   if (n > ((int64_t)1 << 32)) return POLSAR_E_ARG;
   const size_t es = esize(dtype);
   if ((r = check_planes(s, s_pitch, n, es))) return r;

@@ -1,7 +1,7 @@
 // Device helpers shared by the per-call kernels and the batched kernel:
 // 128/64-bit plane access (through generic or global-space pointers), status
 // bytes, counters, the op table mapping (method, precision) to the
-// per-pixel function, the wave-shared FP64 queue of the FP32 compensated
+// per-pixel function, the wave-shared queue of the FP32 compensated
 // form, and a fixed-order block sum.
 #pragma once
 

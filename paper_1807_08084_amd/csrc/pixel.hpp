@@ -192,7 +192,7 @@ PX_HD DW<T> dot3(T x1, T y1, T x2, T y2, T x3, T y3, T& rerr, bool* ordered = nu
   return DW<T>{p, s};
 }
 
-// ordered (FP32 step only, null otherwise): the diagonal cofactors take the
+// ordered (FP32 only, null otherwise): the diagonal cofactors take the
 // FastTwoSum form and clear *ordered where its condition fails.
 template <class T>
 PX_HD void cofactors_comp(const T z[9], DW<T> c[9], T rerr[9], bool* ordered = nullptr) {
@@ -229,7 +229,7 @@ PX_HD void cofactors_comp(const T z[9], DW<T> c[9], T rerr[9], bool* ordered = n
 //   E = (1 + 64u) [u (|det| + R + C) + 64 eta (1 + sum |x_i|)],
 // the (1 + 64u) covering the rounding of R, C and E themselves.  With
 // entries far below 1e-10 in FP32 that term exceeds 1e-6 |det| and the
-// pixel is recomputed in FP64, where nothing underflows.
+// pixel is rerouted: in FP64 nothing of it underflows.
 template <class T>
 PX_HD T det_comp(const T z[9], const DW<T> c[9], const T rerr[9], T& bound) {
 #if defined(__clang__)

@@ -8,9 +8,9 @@
 // all of its 9*U (or 18*U) loads before any arithmetic, then all of its
 // stores.  Pixels are independent; lanes share only the fixed-order
 // reductions of the Wishart sum, the status counters, and the wave's LDS
-// queue of FP32 pixels recomputed in FP64.  This file also holds the fused
-// multilook (per-pixel looks), block-diagonal
-// and out-of-core streaming entry points.
+// queue of FP32 pixels that the quick form leaves over.  This file also holds
+// the fused multilook (per-pixel looks), block-diagonal and out-of-core
+// streaming entry points.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256, OP == ADJ_COMP && sizeof(T) == 4 && U == 1 ? 4
   for (int64_t tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
     const int64_t v0 = tile * (int64_t)(B * U) + threadIdx.x;
     if constexpr (OP == ADJ_COMP && std::is_same<T, float>::value) {
-      // all U vectors through the FP32 step and one shared FP64 queue
+      // all U vectors through the quick form and one shared queue
       extern __shared__ __align__(16) float polsar_dyn_lds[];
       const int w = threadIdx.x >> 6, nw = B >> 6;
       float* q = polsar_dyn_lds + (size_t)w * 64 * U * V * QUEUE_WORDS;
@@ -178,7 +178,7 @@ struct MultilookArgs {
 // an FP64 rounding of the quotient, far below the storage rounding), Z is
 // rounded to the storage type, optionally stored, and inverted exactly as
 // k_inv_det inverts a stored Z (the FP32 compensated form through the
-// wave's FP64 queue).
+// wave's queue).
 template <class T, int OP, int V, bool NT>
 __global__ __launch_bounds__(256) void k_multilook(MultilookArgs a) {
   const T* __restrict__ S = (const T*)a.looks;
@@ -550,7 +550,7 @@ hipError_t go_inv_det(const polsar_launch& c, int64_t grid, InvDetArgs& a, hipSt
 
 // Vectors per lane per tile actually used: the compensated FP32 kernel
 // takes at most two (four run out of registers), and one where the block's
-// shared FP64 queue for two would pass MAX_DYN_LDS.
+// shared queue for two would pass MAX_DYN_LDS.
 template <class T, int OP, int V>
 int inv_det_unroll(const polsar_launch& c) {
   if constexpr (OP == ADJ_COMP && std::is_same<T, float>::value) {

@@ -24,7 +24,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 # the sources the per-call kernels (the inverse among them) are compiled from
-STEP_SOURCES = ("common.hpp", "pixel.hpp", "polsar.hip")
+STEP_SOURCES = ("access.hpp", "common.hpp", "launch.hpp", "pixel.hpp", "polsar.hip")
 
 
 def source_hash(names=STEP_SOURCES) -> str:
@@ -41,7 +41,7 @@ def all_sources_hash() -> str:
 
 
 def _hash_lines() -> str:
-    return (f"# source_hash = {source_hash()}  (common.hpp, pixel.hpp, polsar.hip)\n"
+    return (f"# source_hash = {source_hash()}  ({', '.join(STEP_SOURCES)})\n"
             f"# all_sources_hash = {all_sources_hash()}  (every .hip and .hpp, the batch kernel's included)\n")
 
 
@@ -158,8 +158,8 @@ ROW_KERNELS = [
     ("k_inv_det<float, 3, 2, 1,", "FP32 plain Cholesky", 36, 40),
     ("k_wishart<float, 2, 1,", "FP32 Wishart fwd+bwd", 72, 36),
     ("k_wishart<double, 1, 1,", "FP64 Wishart fwd+bwd", 144, 72),
-    ("k_boxcar<float, 1, 1,", "boxcar 3x3 (halo rows: +2/32 of the reads)", 24, 40),
-    ("k_boxcar<float, 1, 3,", "boxcar 7x7 (halo rows: +6/64 of the reads)", 24, 40),
+    ("k_boxcar<float, 1, 1,", "boxcar 3x3 (excess reads: the strips' two halo rows)", 24, 40),
+    ("k_boxcar<float, 1, 3,", "boxcar 7x7 (excess reads: the strips' six halo rows)", 24, 40),
     ("k_blockdiag<float, 1, 4,", "three-band block-diagonal inverse (27 planes in, 27 + det out)", 108, 112),
     ("k_nlm<float, 0,", "nonlocal means 23x23, KL (Z and its inverse in, filtered Z out)", 72, 36),
     ("k_nlm<float, 1,", "nonlocal means 23x23, Bhattacharyya (Z and det in)", 40, 36),
