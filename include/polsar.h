@@ -325,9 +325,11 @@ void polsar_streamer_destroy(polsar_streamer* s);
  *                more bytes per second with few waves in flight per CU.
  * An entry that was set or tuned runs as it is.  Of a default entry
  * blocks_per_cu is doubled for FP32 compensated calls of op 6 that want
- * statuses or counters and for Wishart calls that write no gradient, one more
- * for such inverse calls of op 0 between 2^20 and 2^22 pixels, and one less for
- * FP32 compensated multilooks of at least 4 looks that store Z.
+ * statuses or counters, for Wishart calls that write no gradient and for
+ * batches that write neither inverses nor gradients; one more for FP32
+ * compensated calls of op 0 between 2^20 and 2^22 pixels that want statuses or
+ * counters, and one less for FP32 compensated multilooks of at least 4 looks
+ * that store Z.
  * Setting a default entry's own values makes it the default again. */
 typedef struct { int block, unroll, grid_per_cu, nontemporal, vector_bytes, blocks_per_cu; } polsar_launch;
 int polsar_get_launch(int op, int dtype, int method, int precision, polsar_launch* out);

@@ -31,6 +31,7 @@
 #include "common.hpp"
 
 size_t polsar_launch_lds_bytes(const polsar_launch& c, size_t need);
+polsar_launch polsar_batch_launch(int dtype, int method, int prec, bool writes);
 
 namespace {
 using namespace polsar_dev;
@@ -345,8 +346,8 @@ int polsar_batch_create(const polsar_image* imgs, int count, int dtype, int meth
   // Launch shape: the batch entry of the launch table (op 3: block, blocks
   // per compute unit, access width, non-temporal); a tile is one vector per
   // lane of one block.
-  polsar_launch use;
-  polsar_get_launch(3, dtype, method, precision, &use);
+  const polsar_launch use =
+      polsar_batch_launch(dtype, method, precision, ops & (POLSAR_OP_INV_DET | POLSAR_OP_WISHART_BWD));
   const int block = use.block;
   const bool half = use.vector_bytes == 8;
   const int VW = (int)((half ? 8 : 16) / es);

@@ -167,6 +167,17 @@ class LaunchTable {
     return c;
   }
 
+  // The batch's launch.  A plan that writes neither inverses nor gradients runs
+  // twice the blocks, as the Wishart kernel does (likelihoods alone, us at the
+  // table's cap and at twice: FP32 20 images of 300x301 30.5, 27.9; 8 of 1024x1024
+  // 115.9, 110.4; FP64 55.0, 45.3 and 224.9, 209.2).
+  polsar_launch batch(int dtype, int method, int prec, bool writes) const {
+    bool standard;
+    polsar_launch c = get(3, dtype, method, prec, &standard);
+    if (standard && !writes) c.blocks_per_cu = std::min(2 * c.blocks_per_cu, 64);
+    return c;
+  }
+
  private:
   mutable std::mutex mu_;
   std::map<std::tuple<int, int, int, int>, polsar_launch> set_;

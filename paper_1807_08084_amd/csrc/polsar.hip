@@ -763,6 +763,11 @@ int64_t max_wishart_partials(int64_t n) { return std::max<int64_t>(1, (n + 63) /
 
 }  // namespace
 
+// The launch of a batch plan (in batch.hip); writes: inverses or gradients.
+polsar_launch polsar_batch_launch(int dtype, int method, int prec, bool writes) {
+  return g_table.batch(dtype, method, prec, writes);
+}
+
 // LDS bytes of a launch with this shape (shared with the batch kernel).
 size_t polsar_launch_lds_bytes(const polsar_launch& c, size_t need) { return launch_lds(c, need); }
 

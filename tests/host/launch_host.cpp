@@ -15,5 +15,8 @@ void host_inv_det(int64_t n, int dtype, int method, int prec, int want_st, polsa
 void host_multilook(int dtype, int method, int prec, int looks, int want_z, polsar_launch* c) {
   *c = table.multilook(dtype, method, prec, looks, want_z);
 }
+void host_batch(int dtype, int method, int prec, int writes, polsar_launch* c) {
+  *c = table.batch(dtype, method, prec, writes);
+}
 void host_wishart(int64_t n, int dtype, int bwd, polsar_launch* c) { *c = table.wishart(n, dtype, bwd); }
 }

@@ -74,3 +74,14 @@ def test_one_more_block_for_statuses_of_middle_sizes(lib, n, want_st, more):
     lib.host_set(*key, ctypes.byref(L.Launch(**dict(default, block=64))))
     assert _run(lib, call) == dict(default, block=64)
     lib.host_set(*key, ctypes.byref(L.Launch(**default)))
+
+
+@pytest.mark.parametrize("dtype", [L.F32, L.F64])
+def test_batch_of_likelihoods_alone(lib, dtype):
+    key = (3, dtype, L.ADJUGATE, L.COMPENSATED)
+    default = _get(lib, key)
+    assert _run(lib, ("batch", key[1:] + (1,))) == default
+    assert _run(lib, ("batch", key[1:] + (0,))) == dict(default, blocks_per_cu=2 * default["blocks_per_cu"])
+    lib.host_set(*key, ctypes.byref(L.Launch(**dict(default, block=64))))
+    assert _run(lib, ("batch", key[1:] + (0,))) == dict(default, block=64)
+    lib.host_set(*key, ctypes.byref(L.Launch(**default)))
